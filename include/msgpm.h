@@ -153,7 +153,8 @@ typedef struct msgpm_layout {
                               -2 - k = filled with plane k (after msgpm_fill) */
   uint64_t loss[2];        /* double: colour-consistency loss of the assignment */
   uint64_t hlabel[2];      /* int32: region plane used for the patch distortion, -1 = identity */
-  uint64_t twin[2];        /* int32: tentative assignment (scratch) */
+  uint64_t twin[2];        /* int32: tentative assignment (scratch; the PatchMatch passes of the
+                              whole-pipeline calls keep patch moments over it and its loss) */
   uint64_t tloss[2];       /* double: its loss (scratch) */
   uint64_t planes;         /* msgpm_plane[n_planes] */
   uint64_t counters;       /* uint64[16][64]: evaluation counters, see below */
@@ -519,7 +520,10 @@ msgpm_status msgpm_check_fp16_arith(int32_t rounds, uint64_t* d_mismatches, void
 
 /* Counters in the workspace (uint64[16][64] at layout.counters: 16 counters,
    each kept as 64 partial sums to be added by the reader), per direction
-   d = 0, 1, reset by msgpm_init_state:
+   d = 0, 1, reset by msgpm_init_state.  A candidate counts when its target
+   differs from the best one at the start of its stage (the whole-pipeline calls:
+   propagation, random search) or batch (single half-sweeps), whether its patch
+   is then read or a bound on its cost already drops it:
      [0 + d] candidates evaluated by the initial PatchMatch pass,
      [2 + d] cost refreshes (also those computed by MSGPM_PM_FRESH
      half-sweeps), [4 + d] candidates of the restricted passes at

@@ -237,6 +237,29 @@ __host__ __device__ inline void cover_range(int n, int B, int nb, int c, int& lo
   if (hi > nb - 1) hi = nb - 1;
 }
 
+// Half-sweeps of a whole pass (search.hip): what a launch is told.  SM_FIRST:
+// the pass's first half-sweep of the colour, which computes the pixels' current
+// costs and ignores what earlier half-sweeps noted; SM_LAST: its last one.
+enum { SM_RESTRICTED = 1, SM_FIRST = 2, SM_LAST = 4 };
+
+// Workgroups over which a half-sweep of one pair is spread before one takes more
+// pixels than a wave has lane groups.  A workgroup's pixels are sorted by work,
+// which needs many of them: with 2048, so that restricted half-sweeps of a
+// 320x240 pair take 7 to 30 pixels per workgroup instead of 64, their
+// distorted-patch part took 4.0 ms per pair instead of 2.8.
+constexpr int kSearchGroups = 512;
+
+// Pixels a workgroup takes when nx of them share cnt pixels of one direction:
+// enough to cover them, and up to 64 once both directions have kSearchGroups
+// workgroups.
+__host__ __device__ inline int search_run(unsigned cnt, int nx, int groups) {
+  unsigned run = (2u * cnt + kSearchGroups - 1) / kSearchGroups;
+  if (run > 64u) run = 64u;
+  if (run < (unsigned)groups) run = groups;
+  const unsigned cover = (cnt + nx - 1) / nx;
+  return (int)(run > cover ? run : cover);
+}
+
 // ---- launch wrappers (defined in the .hip files) ---------------------------
 hipError_t launch_histeq(const DevParams& P, const Ws& w, const float* rgb1, const float* rgb2, hipStream_t s);
 int heq_hist_blocks(const DevParams& P);
@@ -253,6 +276,12 @@ hipError_t launch_pm_halfsweep(const DevParams& P, const Ws& w, int colour, int 
 hipError_t launch_pm_lists(const DevParams& P, const Ws& w, hipStream_t s);
 hipError_t launch_pm_restricted(const DevParams& P, const Ws& w, int colour, int iter, int slot, int ident,
                                 int fresh, hipStream_t s);
+// whole passes: the patch moments of both frames (over the tentative assignment,
+// which a pass does not use), then half-sweeps with SM_* bits; a restricted one
+// over one of the two lists
+hipError_t launch_moments(const DevParams& P, const Ws& w, hipStream_t s);
+hipError_t launch_search(const DevParams& P, const Ws& w, int colour, int iter, int slot, int mode, int ident,
+                         hipStream_t s);
 hipError_t launch_ransac(const DevParams& P, const Ws& w, int level, int stage, hipStream_t s);
 hipError_t launch_assign(const DevParams& P, const Ws& w, int level, int stage, int tentative, hipStream_t s);
 hipError_t launch_symmetry(const DevParams& P, const Ws& w, int level, int stage, hipStream_t s);
@@ -276,8 +305,9 @@ enum BatchKind {
   BK_EVAL_COST_PLANE,  // a = {mode 1 or 2}: region-plane cost refresh
   BK_ZERO_ACTIVE,   // one workgroup per item, grid.y = 1
   BK_ACTIVE_LIST,   // a = {colour}
-  BK_PM_INIT,       // a = {colour, iter, slot, 0 | 2 (fresh: cost computed in the sweep)}
-  BK_PM_RESTRICTED, // a = {colour, iter, slot, 1 | 2 (fresh)}: pixels with a region plane
+  BK_MOMENTS,       // grid.y = frame
+  BK_PM_INIT,       // a = {colour, iter, slot, SM_* bits}
+  BK_PM_RESTRICTED, // the same, pixels with a region plane
   BK_PM_RESTRICTED_IDENT,  // the same, pixels without one
   BK_RANSAC,        // a = {level, stage}
   BK_ASSIGN,        // a = {level, stage, tentative}
@@ -303,6 +333,9 @@ hipError_t launch_batched(int kind, const DevParams& P0, const uint8_t* tab, int
 hipError_t launch_batched_init(int kind, const uint8_t* tab, int k, int grid, BArgs A, hipStream_t s);
 hipError_t launch_batched_pm(int kind, const DevParams& P0, const uint8_t* tab, int k, int grid, BArgs A,
                              bool persist, hipStream_t s);
+hipError_t launch_batched_search(int kind, const DevParams& P0, const uint8_t* tab, int k, int grid, BArgs A,
+                                 bool persist, hipStream_t s);
+int search_batch_blocks(int kind, const DevParams& P);
 hipError_t launch_batched_planes(int kind, const uint8_t* tab, int k, int grid, size_t lds, BArgs A, hipStream_t s);
 size_t ransac_smem_bytes(const DevParams& P, int level);
 // The same for a full B x B window (any frame of at least that size).

@@ -337,48 +337,59 @@ msgpm_status run_lists(const Ctx& c) {
   return check(timed(MSGPM_T_PM_LIST, c.s, [&] { return launch_pm_lists(c.P, c.w, c.s); }), "pm_list");
 }
 
+// The two launches of a restricted half-sweep, launch(ident, stream): pixels with
+// a region plane (ident = 0) and without.  They update disjoint pixels and read
+// only the other colour, so that one after the other they give the same
+// result as side by side (distorted patches on the caller's stream, identity
+// patches on the second one).
+template <class F>
+msgpm_status two_lists(const Ctx& c, F&& launch) {
+  auto run = [&](int ident, hipStream_t s) {
+    return check(timed(ident ? MSGPM_T_PM_RESTRICTED_IDENT : MSGPM_T_PM_RESTRICTED, s, [&] { return launch(ident, s); }),
+                 "pm_restricted");
+  };
+  if (c.one_stream) {
+    msgpm_status st = run(0, c.s);
+    return st != MSGPM_OK ? st : run(1, c.s);
+  }
+  return side_by_side(c.s, [&](hipStream_t s) { return run(0, s); }, [&](hipStream_t s) { return run(1, s); });
+}
+
 // One half-sweep; a restricted one reads the lists run_lists built.  fresh:
 // the swept pixels' current costs are computed in the sweep (the cost refresh
 // of the pass) instead of being read.
 msgpm_status run_halfsweep(const Ctx& c, int colour, int it, int slot, int restricted, int fresh) {
   if (!restricted)
     return check(timed(MSGPM_T_PM_INIT, c.s, [&] { return launch_pm_halfsweep(c.P, c.w, colour, it, slot, fresh, c.s); }), "pm_halfsweep");
-  if (c.one_stream) {
-    // the two launches update disjoint pixels and read only the other colour:
-    // in sequence they give the same result as side by side
-    msgpm_status st = check(timed(MSGPM_T_PM_RESTRICTED, c.s, [&] {
-      return launch_pm_restricted(c.P, c.w, colour, it, slot, 0, fresh, c.s);
-    }), "pm_restricted");
-    if (st != MSGPM_OK) return st;
-    return check(timed(MSGPM_T_PM_RESTRICTED_IDENT, c.s, [&] {
-      return launch_pm_restricted(c.P, c.w, colour, it, slot, 1, fresh, c.s);
-    }), "pm_restricted");
-  }
-  // distorted patches on the caller's stream, identity patches on the second one
-  return side_by_side(
-      c.s,
-      [&](hipStream_t s) {
-        return check(timed(MSGPM_T_PM_RESTRICTED, s, [&] { return launch_pm_restricted(c.P, c.w, colour, it, slot, 0, fresh, s); }), "pm_restricted");
-      },
-      [&](hipStream_t s) {
-        return check(timed(MSGPM_T_PM_RESTRICTED_IDENT, s, [&] { return launch_pm_restricted(c.P, c.w, colour, it, slot, 1, fresh, s); }), "pm_restricted");
-      });
+  return two_lists(c, [&](int ident, hipStream_t s) { return launch_pm_restricted(c.P, c.w, colour, it, slot, ident, fresh, s); });
+}
+
+// SM_* bits of half-sweep `it` of a pass.
+int search_mode(int restricted, int it, int iters) {
+  return (restricted ? SM_RESTRICTED : 0) | (it == 0 ? SM_FIRST : 0) | (it == iters - 1 ? SM_LAST : 0);
 }
 
 // A pass of half-sweeps; a restricted pass reads the lists built before it.
 // The cost refresh that opens the pass (mode 0, or mode 1 for a restricted
 // one) is folded into the first half-sweep of each colour, which computes its
 // pixels' costs before their candidates; a pass without half-sweeps runs it
-// on its own.
+// on its own.  The half-sweeps of a pass note in win what later ones of it need
+// not try again, and bound costs by moments kept over twin and tloss
+// (search.hip), so they run here alone: a half-sweep called by itself
+// (run_halfsweep) leaves both as they are.
 msgpm_status run_pm_pass(const Ctx& c, int slot, int restricted) {
   if (c.P.iters == 0)
     return check(timed(MSGPM_T_EVAL_COST, c.s, [&] { return launch_eval_cost(c.P, c.w, restricted, c.s); }), "eval_cost");
-  for (int it = 0; it < c.P.iters; ++it)
-    for (int colour = 0; colour < 2; ++colour) {
-      msgpm_status st = run_halfsweep(c, colour, it, slot, restricted, it == 0);
-      if (st != MSGPM_OK) return st;
+  msgpm_status st = check(timed(MSGPM_T_FEATURES, c.s, [&] { return launch_moments(c.P, c.w, c.s); }), "moments");
+  for (int it = 0; it < c.P.iters && st == MSGPM_OK; ++it)
+    for (int colour = 0; colour < 2 && st == MSGPM_OK; ++colour) {
+      const int mode = search_mode(restricted, it, c.P.iters);
+      if (!restricted)
+        st = check(timed(MSGPM_T_PM_INIT, c.s, [&] { return launch_search(c.P, c.w, colour, it, slot, mode, 1, c.s); }), "pm_halfsweep");
+      else
+        st = two_lists(c, [&](int ident, hipStream_t s) { return launch_search(c.P, c.w, colour, it, slot, mode, ident, s); });
     }
-  return MSGPM_OK;
+  return st;
 }
 
 }  // namespace
@@ -728,8 +739,10 @@ std::vector<BatchStep> batch_schedule(const DevParams& P) {
   // cost refreshes are folded into the first half-sweep of each colour (run
   // alone when a pass has none)
   if (P.iters == 0) add(BK_EVAL_COST_IDENT, MSGPM_T_EVAL_COST, 0);
+  if (P.iters > 0) add(BK_MOMENTS, MSGPM_T_FEATURES);
   for (int it = 0; it < P.iters; ++it)
-    for (int colour = 0; colour < 2; ++colour) add(BK_PM_INIT, MSGPM_T_PM_INIT, colour, it, 0, it == 0 ? 2 : 0);
+    for (int colour = 0; colour < 2; ++colour)
+      add(BK_PM_INIT, MSGPM_T_PM_INIT, colour, it, 0, search_mode(0, it, P.iters));
   for (int l = 0; l < P.n_levels; ++l) {
     for (int stage = 1; stage <= 2; ++stage) {
       add(BK_RANSAC, MSGPM_T_RANSAC, l, stage);
@@ -748,9 +761,10 @@ std::vector<BatchStep> batch_schedule(const DevParams& P) {
       add(BK_EVAL_COST_IDENT, MSGPM_T_EVAL_COST, 1);
       add(BK_EVAL_COST_PLANE, MSGPM_T_EVAL_COST, 1);
     }
+    if (P.iters > 0) add(BK_MOMENTS, MSGPM_T_FEATURES);
     for (int it = 0; it < P.iters; ++it)
       for (int colour = 0; colour < 2; ++colour) {
-        const int mode = it == 0 ? 3 : 1;
+        const int mode = search_mode(1, it, P.iters);
         add(BK_PM_RESTRICTED, MSGPM_T_PM_RESTRICTED, colour, it, l + 1, mode);
         add(BK_PM_RESTRICTED_IDENT, MSGPM_T_PM_RESTRICTED_IDENT, colour, it, l + 1, mode);
       }

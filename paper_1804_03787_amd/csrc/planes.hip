@@ -1419,6 +1419,7 @@ int batch_blocks(int kind, const DevParams& P, const int* a) {
     case BK_EVAL_COST_PLANE:
     case BK_ZERO_ACTIVE:
     case BK_ACTIVE_LIST:
+    case BK_MOMENTS:
     case BK_PM_INIT:
     case BK_PM_RESTRICTED:
     case BK_PM_RESTRICTED_IDENT:
@@ -1442,10 +1443,12 @@ hipError_t launch_batched(int kind, const DevParams& P0, const uint8_t* tab, int
     case BK_EVAL_COST_PLANE:
     case BK_ZERO_ACTIVE:
     case BK_ACTIVE_LIST:
+      return launch_batched_pm(kind, P0, tab, k, grid, A, persist, s);
+    case BK_MOMENTS:
     case BK_PM_INIT:
     case BK_PM_RESTRICTED:
     case BK_PM_RESTRICTED_IDENT:
-      return launch_batched_pm(kind, P0, tab, k, grid, A, persist, s);
+      return launch_batched_search(kind, P0, tab, k, grid, A, persist, s);
     default:
       return launch_batched_planes(kind, tab, k, grid, lds, A, s);
   }

@@ -1,0 +1,775 @@
+// PatchMatch passes of the whole pipeline: half-sweeps that evaluate only the
+// candidates that could win.
+//
+// A half-sweep gives every pixel the best of its current offset, its four
+// neighbours' offsets, the plane candidate (distorted patches) and the random
+// search around the best of those, a candidate replacing the best only if its
+// FP32 cost (patch.h) is strictly lower.  Within a pass three exact
+// arguments drop candidates before any of their patch is read:
+//
+//  * Unchanged neighbours.  A pixel keeps in its (otherwise constant) win entry
+//    whether its last half-sweep changed its offset.  The offset of a
+//    neighbour that did not change was offered in the pixel's previous
+//    half-sweep of this pass and did not beat a best that has only fallen
+//    since.  The plane candidate is the same all through a pass, so it is
+//    evaluated in the first half-sweep alone.
+//  * Targets tried before.  The same entry holds the positions of the 5x5
+//    neighbourhood of the best that random search tried since the best was
+//    set: the smallest radii draw them again and again.
+//  * A lower bound from patch moments.  The SSD of two patches is at least the
+//    squared distance of their projections on any orthonormal functions; here
+//    the mean, the x and y slope and the x y term of the colour channels,
+//    stored per pixel in 12 bytes (k_moments).  One 12-byte load per candidate,
+//    made by one lane, stands in for the first rows of its patch: at 1024x436
+//    it drops over nine tenths of the random targets at radii of 32 pixels and
+//    more.  For a distorted patch the bound is lowered by what the distortion
+//    can change, from a measure of the target's roughness kept beside the
+//    moments.
+//
+// A pixel's candidate of the lowest bound is evaluated first, so that the others
+// meet the lowest cost there is to be found; equal costs go to the candidate
+// offered first, as in a one-at-a-time loop.
+//
+// What is left is evaluated by lane groups as everywhere else (a pixel by 2r+1
+// lanes), so the accepted costs are the same bits.  A workgroup owns up to 64
+// pixels: its lanes, one per candidate, propose and filter; then the pixels with
+// work, sorted by their number of candidates so that the groups of a wave finish
+// together, go to the lane groups of its four waves.  The two phases run twice,
+// for propagation and for random search, and meet in LDS.
+#include "patch.h"
+
+#pragma clang fp contract(off)
+
+namespace msgpm {
+
+// win entry of an unassigned pixel during a pass: the sign, whether its last
+// half-sweep changed its offset, and the tried positions around its best
+// ((dy + 2) * 5 + dx + 2).  -1, the value outside passes, reads as changed.
+constexpr unsigned kMemoSign = 0x80000000u, kMemoChanged = 1u << 25, kMemoTried = (1u << 25) - 1u;
+
+constexpr int kTgtRows = 16;          // random-search radii: at most 15; neighbours and plane: 5
+constexpr unsigned kRefresh = 1u << 31;  // in a candidate mask: the current cost first
+
+constexpr int kSlots = 64;  // pixels of a workgroup
+
+struct SearchLds {
+  int tgt[kTgtRows][kSlots];  // candidate targets x | y << 16
+  int pix[kSlots];            // x | y << 16
+  int best0[kSlots], best1[kSlots];  // best target before the half-sweep, after propagation
+  int best[kSlots];           // best target
+  float bc[kSlots];           // its cost
+  unsigned mask[kSlots];      // candidates to evaluate
+  unsigned key[kSlots];       // the candidate of the lowest bound (its number in the low 4 bits)
+  unsigned memo[kSlots];      // tried positions around the best
+  float shift[kSlots];        // of the distortion bound
+  int order[kSlots];          // pixels with work, most candidates first
+  int n;                      // pixels, then pixels with work
+  uint16_t lb[kTgtRows][kSlots];  // candidates' cost bounds (upper half of an FP32)
+};
+
+__device__ inline int pack_xy(int x, int y) { return x | (y << 16); }
+__device__ inline int xy_x(int v) { return v & 0xffff; }
+__device__ inline int xy_y(int v) { return (int)((unsigned)v >> 16); }
+
+// ---------------------------------------------------------------------------
+// Patch moments
+// ---------------------------------------------------------------------------
+// Per pixel and colour channel the projections of its (border-clamped) patch
+// on the orthonormal functions 1/T, x/sqrt(T n), y/sqrt(T n), x y/n (T = 2r+1,
+// n = sum of x^2 over a row; the last not for blue), quantised to int8 in units
+// of 1/scale: word c of a pixel holds channel c's.  The pixel values are first
+// moved by the centre and cut to twice the half range of a sample of both
+// frames, then the moments are cut to +-127 units; both cuts bring two values
+// closer or leave their distance, so the bound below holds whatever the sample
+// gave.  Rounding moves each component of a difference by at most 1 unit (FP32
+// sums add under 0.01), so two patches whose stored vectors are D apart are at
+// least (D - sqrt(11) - 0.01) / scale apart, and their SSD is at least the square.
+//
+// A distorted patch samples the target at d + a(d) instead of d.  With |a| <= 1
+// along both axes, bilinear interpolation differs from the pixel at d by at
+// most |ax| hx + |ay| hy per channel, hx the largest difference of horizontal
+// neighbours at that pixel and at the rows above and below, hy that of its
+// vertical ones.  So if |a(d)| <= b |d| at every tap, the sampled patch is at
+// most b K from the undistorted one, K^2 the sum of |d|^2 (hx^2 + hy^2) over
+// the patch.  The last byte of a pixel holds K, rounded up, in units of
+// kRough / scale; 255: larger, or not known.
+constexpr int kMomW = 32, kMomH = 8;  // pixels of a workgroup's tile
+constexpr float kMomSlack = 3.3267f;  // sqrt(11) + 0.01
+constexpr float kRough = 4.0f;
+
+template <int R>
+struct MomLds {
+  static constexpr int TW = kMomW + 2 * R, TH = kMomH + 2 * R;
+  float v[3][TH + 2][TW + 2];
+  float h2[TH][TW];
+  float s0[3][TH][kMomW], s1[3][TH][kMomW], q0[TH][kMomW], q2[TH][kMomW];
+  float red[2][kBlock / kWave];
+};
+
+__device__ inline float rgb_value(const DevParams& P, const void* F, size_t i) {
+  return P.fp16 ? __half2float(reinterpret_cast<const __half*>(F)[i]) : reinterpret_cast<const float*>(F)[i];
+}
+
+// Centre and half range of a fixed sample of both frames' colours, the same in
+// every workgroup: half the threads read each frame.
+__device__ inline void moment_range(const DevParams& P, const Ws& w, int stride, float (&red)[2][kBlock / kWave],
+                                    float& centre, float& half) {
+  const int t = threadIdx.x;
+  const size_t p = (size_t)(((long long)P.W * P.H * (2 * (t & 127) + 1)) >> 8);
+  float lo = __builtin_huge_valf(), hi = -__builtin_huge_valf();
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const float v = rgb_value(P, w.feat[t >> 7], p * stride + c);
+    lo = fminf(lo, v);
+    hi = fmaxf(hi, v);
+  }
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    lo = fminf(lo, __shfl_xor(lo, o));
+    hi = fmaxf(hi, __shfl_xor(hi, o));
+  }
+  if ((t & (kWave - 1)) == 0) {
+    red[0][t / kWave] = lo;
+    red[1][t / kWave] = hi;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kBlock / kWave; ++i) {
+    lo = fminf(lo, red[0][i]);
+    hi = fmaxf(hi, red[1][i]);
+  }
+  centre = 0.5f * (lo + hi);
+  half = 0.5f * (hi - lo);
+}
+
+// bk.y = frame.  The moments of frame f go where the tentative assignment of
+// direction f is kept, which is free during a PatchMatch pass: its labels and
+// its losses lie one after the other, 12 bytes per pixel.
+template <int R>
+__device__ __forceinline__ void moments_body(const DevParams& P, const Ws& w, Blk bk) {
+  constexpr int T = 2 * R + 1, TW = MomLds<R>::TW, TH = MomLds<R>::TH;
+  __shared__ MomLds<R> S;
+  const int f = bk.y, t = threadIdx.x, W = P.W, H = P.H;
+  const int stride = P.fp16 ? (P.C == 3 ? 4 : 6) : P.C;
+  float centre, half;
+  moment_range(P, w, stride, S.red, centre, half);
+  // 127 units reach 0.8 of the largest mean moment.  No usable range (a flat
+  // sample, or values that are not finite): scale 0, which bounds nothing.
+  const bool usable = half > 1e-15f && half < 1e15f;
+  const float scale = usable ? 127.0f / (0.8f * (float)T * half) : 0.0f;
+  if (bk.x == 0 && f == 0 && t == 0) w.act_count[8] = __float_as_uint(scale);
+  const int ntx = (W + kMomW - 1) / kMomW;
+  const int x0 = (bk.x % ntx) * kMomW, y0 = (bk.x / ntx) * kMomH;
+  const float cut = 2.0f * half;
+  for (int i = t; i < (TW + 2) * (TH + 2); i += kBlock) {
+    const int ly = i / (TW + 2), lx = i - ly * (TW + 2);
+    const size_t o = (size_t)(clampi(y0 + ly - R - 1, 0, H - 1) * W + clampi(x0 + lx - R - 1, 0, W - 1)) * stride;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) S.v[c][ly][lx] = rgb_value(P, w.feat[f], o + c);
+  }
+  __syncthreads();
+  for (int i = t; i < TW * TH; i += kBlock) {
+    const int ly = i / TW + 1, lx = i % TW + 1;
+    float e = 0.f;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      float hx = 0.f;
+#pragma unroll
+      for (int d = -1; d <= 1; ++d) {
+        const float m = S.v[c][ly + d][lx];
+        hx = fmaxf(hx, fmaxf(fabsf(S.v[c][ly + d][lx - 1] - m), fabsf(S.v[c][ly + d][lx + 1] - m)));
+      }
+      const float m = S.v[c][ly][lx];
+      const float hy = fmaxf(fabsf(S.v[c][ly - 1][lx] - m), fabsf(S.v[c][ly + 1][lx] - m));
+      hx *= scale;
+      e = fmaf(hx, hx, fmaf(hy * scale, hy * scale, e));
+    }
+    S.h2[ly - 1][lx - 1] = e;
+  }
+  for (int i = t; i < 3 * TH * kMomW; i += kBlock) {
+    const int lx = i % kMomW, ly = (i / kMomW) % TH, c = i / (kMomW * TH);
+    float a = 0.f, b = 0.f;
+#pragma unroll
+    for (int d = 0; d < T; ++d) {
+      const float v = fminf(fmaxf(S.v[c][ly + 1][lx + d + 1] - centre, -cut), cut) * scale;
+      a += v;
+      b = fmaf((float)(d - R), v, b);
+    }
+    S.s0[c][ly][lx] = a;
+    S.s1[c][ly][lx] = b;
+  }
+  __syncthreads();
+  for (int i = t; i < TH * kMomW; i += kBlock) {
+    const int lx = i % kMomW, ly = i / kMomW;
+    float a = 0.f, b = 0.f;
+#pragma unroll
+    for (int d = 0; d < T; ++d) {
+      const float v = S.h2[ly][lx + d];
+      a += v;
+      b = fmaf((float)((d - R) * (d - R)), v, b);
+    }
+    S.q0[ly][lx] = a;
+    S.q2[ly][lx] = b;
+  }
+  __syncthreads();
+  const int lx = t % kMomW, ly = t / kMomW, x = x0 + lx, y = y0 + ly;
+  if (x >= W || y >= H) return;
+  constexpr float nx = (float)(R * (R + 1) * T) / 3.0f;
+  const float k0 = 1.0f / (float)T, k1 = rsqrtf(nx * (float)T), k2 = 1.0f / nx;
+  uint32_t word[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    float m = 0.f, mx = 0.f, my = 0.f, mxy = 0.f;
+#pragma unroll
+    for (int d = 0; d < T; ++d) {
+      const float a = S.s0[c][ly + d][lx], b = S.s1[c][ly + d][lx], yy = (float)(d - R);
+      m += a;
+      mx += b;
+      my = fmaf(yy, a, my);
+      mxy = fmaf(yy, b, mxy);
+    }
+    const float q[4] = {m * k0, mx * k1, my * k1, mxy * k2};
+    uint32_t u = 0;
+#pragma unroll
+    for (int i = 0; i < (c < 2 ? 4 : 3); ++i)
+      u |= ((uint32_t)(int)rintf(fminf(fmaxf(q[i], -127.f), 127.f)) & 0xffu) << (8 * i);
+    word[c] = u;
+  }
+  float k2sum = 0.f;
+#pragma unroll
+  for (int d = 0; d < T; ++d)
+    k2sum += fmaf((float)((d - R) * (d - R)), S.q0[ly + d][lx], S.q2[ly + d][lx]);
+  const float rough = sqrtf(k2sum) * (1.0001f / kRough);
+  word[2] |= (rough < 254.f ? (uint32_t)(int)ceilf(rough) : 255u) << 24;
+  uint32_t* out = reinterpret_cast<uint32_t*>(w.twin[f]) + 3 * (size_t)(y * W + x);
+  out[0] = word[0];
+  out[1] = word[1];
+  out[2] = word[2];
+}
+
+template <int R>
+__global__ __launch_bounds__(kBlock) void k_moments(DevParams P, Ws w) {
+  moments_body<R>(P, w, blk_here());
+}
+
+template <int R>
+__global__ __launch_bounds__(kBlock) void kb_moments(const uint8_t* __restrict__ tab, int k) {
+  const BatchView V = batch_view(tab, k);
+  const PairDesc* __restrict__ pd = V.pd;
+  const Item* __restrict__ it = V.it;
+  const int n = V.n, total = V.total;
+  for_each_item<true>(it, n, total, [&](int i, Blk bk) {
+    moments_body<R>(pd[it[i].pair].P, pd[it[i].pair].w, bk);
+  });
+}
+
+static int moments_blocks(const DevParams& P) {
+  return ((P.W + kMomW - 1) / kMomW) * ((P.H + kMomH - 1) / kMomH);
+}
+
+// One frame's moments through a buffer resource (32-bit byte offsets: 12 bytes
+// for each of at most 2^28 pixels).
+struct Moments {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ inline u32x3 at(int p) const { return __builtin_amdgcn_raw_buffer_load_b96(r, p * 12, 0, 0); }
+};
+__device__ inline Moments moments_buf(const Ws& w, int f, int n) {
+  return Moments{__builtin_amdgcn_make_buffer_rsrc(w.twin[f], (short)0, (int)((unsigned)n * 12u), 0x00020000)};
+}
+
+__device__ inline int dot4(uint32_t a, uint32_t b, int c) {
+  return __builtin_amdgcn_sdot4((int)a, (int)b, c, false);
+}
+// Squared distance of two pixels' moments (the last byte is not one).
+__device__ inline int moments_norm2(u32x3 a) {
+  const uint32_t z = a.z & 0xffffffu;
+  return dot4(a.x, a.x, dot4(a.y, a.y, dot4(z, z, 0)));
+}
+
+// ---------------------------------------------------------------------------
+// Half-sweep
+// ---------------------------------------------------------------------------
+
+// What bounds the costs of a pixel's candidates.
+struct Bound {
+  u32x3 src;    // the pixel's moments, without the last byte
+  int src2;     // their squared norm
+  float shift;  // b of the pixel's distortion, in units of kRough; infinite: no bound
+  float unit2;  // squared length of a unit, less what the cost may be under the exact SSD
+};
+
+// Largest |a(d)| / |d| of the distortion of plane H at (x, y), a(d) = Delta(d) - d
+// with Delta(d) = M d / (1 + g d): (|M - I| + |g| |d|) / (1 - |g| |d|) in the
+// spectral norm, |d| at most sqrt(2) r; infinite where that leaves |a| <= 1.
+__device__ inline float distortion(const double* H, int x, int y, int r) {
+  const double w = H[6] * x + H[7] * y + H[8];
+  const float inf = __builtin_huge_valf();
+  if (!(w > 0)) return inf;
+  const double qx = (H[0] * x + H[1] * y + H[2]) / w, qy = (H[3] * x + H[4] * y + H[5]) / w;
+  const double g0 = H[6] / w, g1 = H[7] / w;
+  const float a = (float)(H[0] / w - qx * g0 - 1.0), b = (float)(H[1] / w - qx * g1);
+  const float c = (float)(H[3] / w - qy * g0), d = (float)(H[4] / w - qy * g1 - 1.0);
+  const float s = fmaf(a, a, b * b) + fmaf(c, c, d * d), det = a * d - b * c;
+  const float norm = sqrtf(0.5f * (s + sqrtf(fmaxf(s * s - 4.f * det * det, 0.f))));
+  const float reach = 1.4143f * (float)r, g = sqrtf((float)(g0 * g0 + g1 * g1)) * reach;
+  if (!(g < 0.5f)) return inf;
+  const float v = (norm + g) / (1.f - g) * 1.001f + 1e-4f;
+  return v * reach < 1.f ? v : inf;
+}
+
+__device__ inline Bound make_bound(const Moments& M1, int p, float shift, float scale) {
+  Bound f;
+  f.src = M1.at(p);
+  f.src.z &= 0xffffffu;
+  f.src2 = moments_norm2(f.src);
+  f.shift = shift * kRough;
+  f.unit2 = scale > 0.f ? 0.9999f / (scale * scale) : 0.f;
+  return f;
+}
+
+// A cost that target p's cannot be below, or 0.
+__device__ inline float cost_bound(const Bound& f, const Moments& M2, int p) {
+  const u32x3 t = M2.at(p);
+  const int dot = dot4(f.src.x, t.x, dot4(f.src.y, t.y, dot4(f.src.z, t.z, 0)));
+  const float d = sqrtf((float)(f.src2 + moments_norm2(t) - 2 * dot));
+  const uint32_t rough = t.z >> 24;
+  const float less = f.shift > 0.f ? f.shift * (rough == 255u ? __builtin_huge_valf() : (float)rough) : 0.f;
+  const float v = d - kMomSlack - less;
+  return v > 0.f ? v * v * f.unit2 : 0.f;  // less infinite or not a number: 0
+}
+
+// Random-search target k of pixel p around target (bx, by).
+__device__ inline void draw_target(const DevParams& P, int p, int bx, int by, int k, int iter, uint64_t w3, int& tx,
+                                   int& ty) {
+  const int Rk = P.R0 >> k;
+  uint64_t c[4] = {(uint64_t)(uint32_t)p, (uint64_t)k, (uint64_t)iter, w3};
+  philox4x64(c, P.seed, 0);
+  tx = clampi(bx + draw_below(c[0], (uint32_t)(2 * Rk + 1)) - Rk, 0, P.W - 1);
+  ty = clampi(by + draw_below(c[1], (uint32_t)(2 * Rk + 1)) - Rk, 0, P.H - 1);
+}
+
+// The bit of target (tx, ty) among the tried positions around (bx, by), 0 if outside.
+__device__ inline unsigned tried_bit(int tx, int ty, int bx, int by) {
+  const unsigned ux = (unsigned)(tx - bx + 2), uy = (unsigned)(ty - by + 2);
+  return ux < 5u && uy < 5u ? 1u << (uy * 5u + ux) : 0u;
+}
+constexpr unsigned kTriedCentre = 1u << 12;
+
+// A candidate's bound as kept in LDS, rounded down, and the key that orders a
+// pixel's candidates by it.
+__device__ inline uint16_t bound_bits(float v) { return (uint16_t)(__float_as_uint(v) >> 16); }
+__device__ inline unsigned bound_key(float v, int k) { return (__float_as_uint(v) & ~15u) | (unsigned)k; }
+
+// Evaluates the candidates of the n listed pixels, one pixel per lane group at a
+// time, the waves taking the list in turn; rows: tap rows computed (counted at
+// the group's last lane).
+template <int R, int C, bool FP16, bool IDENT>
+__device__ inline void evaluate(const DevParams& P, const Ws& w, int dir, SearchLds& S, int n, unsigned& rows_out) {
+  constexpr int G = 2 * R + 1, NG = kWave / G;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int g = lane / G, j = lane - g * G, base = g * G;
+  const int W = P.W, H = P.H;
+  const float gw = P.gw;
+  const Feat F1 = feat_buf<C, FP16>(w.feat[dir], W, H), F2 = feat_buf<C, FP16>(w.feat[1 - dir], W, H);
+  for (int i0 = wave * NG; i0 < n; i0 += NG * (kBlock / kWave)) {
+    const int i = i0 + g;
+    if (g >= NG || i >= n) continue;
+    const int sl = S.order[i];
+    const int pix = S.pix[sl];
+    const int x = xy_x(pix), y = xy_y(pix);
+    int best = S.best[sl], kbest = -1;
+    float bc = S.bc[sl];
+    unsigned m = S.mask[sl], rows = 0;
+    const unsigned key = S.key[sl];
+    LaneCol<R, C, IDENT> L;
+    int geo = 1;
+    if constexpr (IDENT) {
+      L.dx = j - R;
+    } else {
+      const double* Hp = plane_H(w, w.hlabel[dir][y * W + x]);
+      bool integral;
+      const bool ok = setup_geometry<R, C, false>(L, Hp, x, y, j - R, 4.0f * (float)(W > H ? W : H), integral);
+      geo = group_geometry<G>(ok, integral, base);
+    }
+    // geo 2: a homogeneous coordinate is not positive, every cost is +inf
+    if (geo != 2) load_column<R, C, FP16, IDENT>(L, F1, W, H, x, y, j - R);
+    if (m & kRefresh) {
+      bool rejected;
+      unsigned r0 = 0;
+      if (geo == 2)
+        bc = __builtin_huge_valf();
+      else if (IDENT || geo == 1)
+        bc = group_cost<R, C, FP16, IDENT, true, false>(L, F2, W, H, xy_x(best), xy_y(best), gw, base, 0.f, rejected, r0);
+      else
+        bc = group_cost<R, C, FP16, IDENT, IDENT, false>(L, F2, W, H, xy_x(best), xy_y(best), gw, base, 0.f, rejected, r0);
+    }
+    m &= geo == 2 ? 0u : ~kRefresh;
+    // the candidate of the lowest bound, then the others in order.  A cost equal
+    // to the best one wins only before the candidate that holds it.
+    int k = (int)(key & 15u);
+    while (m) {
+      if (!((m >> k) & 1u)) k = __builtin_ctz(m);
+      m &= ~(1u << k);
+      const int t = S.tgt[k][sl];
+      const float lb = __uint_as_float((unsigned)S.lb[k][sl] << 16);
+      const float top = k < kbest ? __uint_as_float(__float_as_uint(bc) + 1u) : bc;
+      bool won;
+      float c = 0.f;
+      if constexpr (IDENT) {
+        // comparisons at the group's last lane, where bc is exact
+        won = group_flag<G>(lb < top, base) && t != best;
+        if (won) {
+          // all rows at once: a check on the way would drop few that the bound
+          // has left (at 1024x436, after row 6 of 9, one in seven)
+          c = group_chain<G>(ident_rows1<R, C, FP16, 0, G>(0.f, L, F2, W, H, xy_x(t), xy_y(t), gw));
+          won = group_flag<G>(c < top, base);
+          rows += G;
+        }
+      } else {
+        won = lb < top && t != best;
+        if (won) {
+          bool rejected;
+          if (geo == 1)
+            c = group_cost<R, C, FP16, IDENT, true, true>(L, F2, W, H, xy_x(t), xy_y(t), gw, base, top, rejected, rows);
+          else
+            c = group_cost<R, C, FP16, IDENT, IDENT, true>(L, F2, W, H, xy_x(t), xy_y(t), gw, base, top, rejected, rows);
+          won = !rejected && c < top;
+        }
+      }
+      if (won) {
+        bc = c;
+        best = t;
+        kbest = k;
+      }
+    }
+    if (j == G - 1) {
+      S.best[sl] = best;
+      S.bc[sl] = bc;
+      rows_out += rows;
+    }
+  }
+}
+
+// Lists the np pixels with work in S.order, most candidates first, and puts their
+// number in S.n; called by one wave.
+__device__ inline void sort_by_work(SearchLds& S, int np) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int cnt = lane < np ? __popc(S.mask[lane]) : 0;
+  const unsigned long long lt = (1ull << lane) - 1ull;
+  int n = 0;
+  for (int c = kTgtRows; c > 0; --c) {
+    const unsigned long long m = __ballot(cnt == c);
+    if (cnt == c) S.order[n + __popcll(m & lt)] = lane;
+    n += __popcll(m);
+  }
+  if (lane == 0) S.n = n;
+}
+
+// Adds candidate k at target (tx, ty) of slot sl with cost bound lb.
+__device__ inline void add_candidate(SearchLds& S, int sl, int k, int tx, int ty, float lb) {
+  S.tgt[k][sl] = pack_xy(tx, ty);
+  S.lb[k][sl] = bound_bits(lb);
+  atomicMin(&S.key[sl], bound_key(lb, k));
+  atomicOr(&S.mask[sl], 1u << k);
+}
+
+// State of slot sl's pixel before propagation.
+template <int R, bool IDENT>
+__device__ inline void open_slot(const DevParams& P, const Ws& w, int dir, SearchLds& S, int sl, int x, int y,
+                                 bool first) {
+  const int p = y * P.W + x;
+  const int32_t v = w.nnf[dir][p];
+  const int best = pack_xy(x + off_dx(v), y + off_dy(v));
+  S.pix[sl] = pack_xy(x, y);
+  S.best0[sl] = best;
+  S.best[sl] = best;
+  S.bc[sl] = first ? 0.f : w.cost[dir][p];
+  S.memo[sl] = first ? 0u : (unsigned)w.win[dir][p] & kMemoTried;
+  S.mask[sl] = first ? kRefresh : 0u;
+  S.key[sl] = ~0u;
+  if constexpr (!IDENT) S.shift[sl] = distortion(plane_H(w, w.hlabel[dir][p]), x, y, R);
+}
+
+// Candidate k of propagation: the neighbours' offsets (left, right, up, down), then
+// (distorted patches) the target where the region plane sends the pixel, rounded
+// to the grid.
+template <bool IDENT>
+__device__ inline void offer_neighbour(const DevParams& P, const Ws& w, int dir, SearchLds& S, int sl, int k,
+                                       bool first, const Moments& M1, const Moments& M2, float scale,
+                                       unsigned& evals) {
+  const int W = P.W, H = P.H, pix = S.pix[sl], x = xy_x(pix), y = xy_y(pix), p = y * W + x;
+  int tx, ty;
+  bool need = true;
+  if (IDENT || k < 4) {
+    const int nx = x + (k == 0 ? -1 : (k == 1 ? 1 : 0));
+    const int ny = y + (k == 2 ? -1 : (k == 3 ? 1 : 0));
+    if (nx < 0 || nx >= W || ny < 0 || ny >= H) return;
+    const int q = ny * W + nx;
+    const int32_t v = w.nnf[dir][q];
+    tx = clampi(x + off_dx(v), 0, W - 1);
+    ty = clampi(y + off_dy(v), 0, H - 1);
+    if (!first) {
+      const int m = w.win[dir][q];
+      need = m < 0 && (m & (int)kMemoChanged);
+    }
+  } else {
+    const double* Hp = plane_H(w, w.hlabel[dir][p]);
+    const double ww = Hp[6] * x + Hp[7] * y + Hp[8];
+    if (!(ww > 0)) return;
+    const double qx = (Hp[0] * x + Hp[1] * y + Hp[2]) / ww;
+    const double qy = (Hp[3] * x + Hp[4] * y + Hp[5]) / ww;
+    const double dl = (double)(4.0f * (float)(W > H ? W : H));
+    double rx = floor(qx + 0.5), ry = floor(qy + 0.5);
+    rx = rx < -dl ? -dl : (rx > dl ? dl : rx);
+    ry = ry < -dl ? -dl : (ry > dl ? dl : ry);
+    tx = clampi((int)rx, 0, W - 1);
+    ty = clampi((int)ry, 0, H - 1);
+    need = first;
+  }
+  if (pack_xy(tx, ty) == S.best0[sl]) return;
+  ++evals;
+  if (!need) return;
+  // the bounds drop few of these candidates but in the first half-sweep, where
+  // the best may still be a random one
+  float lb = 0.f;
+  if (first) lb = cost_bound(make_bound(M1, p, IDENT ? 0.f : S.shift[sl], scale), M2, ty * W + tx);
+  add_candidate(S, sl, k, tx, ty, lb);
+}
+
+// Candidate k of random search, around the best after propagation.
+template <bool IDENT>
+__device__ inline void offer_random(const DevParams& P, SearchLds& S, int sl, int k, int iter, uint64_t w3,
+                                    const Moments& M1, const Moments& M2, float scale, unsigned& evals) {
+  const int W = P.W, pix = S.pix[sl], p = xy_y(pix) * W + xy_x(pix);
+  const int b = S.best[sl], bx = xy_x(b), by = xy_y(b);
+  int tx, ty;
+  draw_target(P, p, bx, by, k, iter, w3, tx, ty);
+  const unsigned bit = tried_bit(tx, ty, bx, by);
+  if (bit == kTriedCentre) return;
+  ++evals;
+  // of lanes that draw one position together, the first to note it keeps it
+  if (bit && (atomicOr(&S.memo[sl], bit) & bit)) return;
+  const float lb = cost_bound(make_bound(M1, p, IDENT ? 0.f : S.shift[sl], scale), M2, ty * W + tx);
+  if (lb >= S.bc[sl]) return;
+  add_candidate(S, sl, k, tx, ty, lb);
+}
+
+// Calls f(slot, k) for every slot < np and k < nk, the lanes of the workgroup
+// taking the pairs in turn; k is the same for all lanes of a wave (and scalar)
+// when the workgroup is full.
+template <class F>
+__device__ inline void each_candidate(int np, int nk, F&& f) {
+  if (np == kSlots) {
+    for (int k = __builtin_amdgcn_readfirstlane(threadIdx.x / kSlots); k < nk; k += kBlock / kSlots)
+      f((int)threadIdx.x % kSlots, k);
+  } else {
+    for (int i = threadIdx.x; i < np * nk; i += kBlock) {
+      const int k = i / np;
+      f(i - k * np, k);
+    }
+  }
+}
+
+// Rows of the 16-pixel wide tiles into which nx workgroups divide a frame, one
+// per tile (8 pixels of a colour per row, whose patches overlap); 0: they do not.
+__host__ __device__ inline int tile_rows(int W, int H, int nx) {
+  for (int rows = 8; rows; rows >>= 1)
+    if (((W + 15) >> 4) * ((H + rows - 1) / rows) == nx) return rows;
+  return 0;
+}
+
+// mode: SM_* bits.  Unrestricted: the pixels of one colour, in tiles when the
+// launch has a workgroup per tile, otherwise in runs.  Restricted: the listed
+// pixels.
+template <int R, int C, bool FP16, bool IDENT>
+__device__ __forceinline__ void search_body(const DevParams& P, const Ws& w, Blk bk, int colour, int iter, int slot,
+                                            int mode) {
+  constexpr int G = 2 * R + 1, NG = kWave / G;
+  __shared__ SearchLds S;
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+  const int dir = bk.y;
+  const int W = P.W, H = P.H, Wh = (W + 1) >> 1;
+  const bool restricted = (mode & SM_RESTRICTED) != 0, first = (mode & SM_FIRST) != 0;
+  const unsigned cap = (unsigned)Wh * (unsigned)H;
+  const unsigned cnt = restricted ? w.act_count[2 * (2 * dir + colour) + (IDENT ? 1 : 0)] : cap;
+  const int rows = restricted ? 0 : tile_rows(W, H, bk.nx);
+  const int run = rows ? 8 * rows : search_run(cnt, bk.nx, NG);
+  const int nb = rows ? bk.nx : (int)((cnt + run - 1) / run);
+  if (bk.x >= nb) return;
+  if (wave == 0) {
+    const unsigned b = (unsigned)xcd_remap(bk.x, nb), i = b * run + lane;
+    int x, y;
+    bool act = lane < run;
+    if (rows) {
+      const int ntx = (W + 15) >> 4;
+      y = (int)(b / ntx) * rows + (lane >> 3);
+      x = (int)(b % ntx) * 16 + 2 * (lane & 7) + ((y + colour) & 1);
+      act = act && x < W && y < H;
+    } else if (restricted) {
+      act = act && i < cnt;
+      const int q = act ? w.act[2 * dir + colour][IDENT ? cap - 1u - i : i] : 0;
+      y = q / W;
+      x = q - y * W;
+    } else {
+      y = (int)(i / Wh);
+      x = 2 * (int)(i - (unsigned)y * Wh) + ((y + colour) & 1);
+      act = act && i < cap && x < W;
+    }
+    const unsigned long long on = __ballot(act);
+    if (act) open_slot<R, IDENT>(P, w, dir, S, __popcll(on & ((1ull << lane) - 1ull)), x, y, first);
+    if (lane == 0) S.n = __popcll(on);
+  }
+  __syncthreads();
+  const int np = S.n;
+  const float scale = __uint_as_float(w.act_count[8]);
+  const Moments M1 = moments_buf(w, dir, W * H), M2 = moments_buf(w, 1 - dir, W * H);
+  const uint64_t w3 = rng_word3(2, dir, slot, 0);
+  unsigned evals = 0, tap_rows = 0;
+#pragma unroll 1
+  for (int random = 0; random < 2; ++random) {
+    if (!random)
+      each_candidate(np, IDENT ? 4 : 5, [&](int sl, int k) {
+        offer_neighbour<IDENT>(P, w, dir, S, sl, k, first, M1, M2, scale, evals);
+      });
+    else
+      each_candidate(np, P.nk, [&](int sl, int k) {
+        offer_random<IDENT>(P, S, sl, k, iter, w3, M1, M2, scale, evals);
+      });
+    __syncthreads();
+    if (wave == 0) sort_by_work(S, np);
+    __syncthreads();
+    evaluate<R, C, FP16, IDENT>(P, w, dir, S, S.n, tap_rows);
+    __syncthreads();
+    if (!random) {
+      if (t < np) {
+        const int best = S.best[t];
+        S.best1[t] = best;
+        if (best != S.best0[t]) S.memo[t] = 0;
+        S.mask[t] = 0;
+        S.key[t] = ~0u;
+      }
+      __syncthreads();
+    }
+  }
+  if (t < np) {
+    const int pix = S.pix[t], x = xy_x(pix), y = xy_y(pix), p = y * W + x;
+    const int best = S.best[t];
+    const bool changed = best != S.best0[t];
+    if (changed) w.nnf[dir][p] = pack_off(xy_x(best) - x, xy_y(best) - y);
+    if (changed || first) w.cost[dir][p] = S.bc[t];
+    const unsigned tried = best == S.best1[t] ? S.memo[t] : 0u;
+    w.win[dir][p] = mode & SM_LAST ? -1 : (int)(kMemoSign | (changed ? kMemoChanged : 0u) | tried);
+  }
+  count_evals<true>(w.counters, (restricted ? (IDENT ? 10 : 4) : 0) + dir, evals);
+  count_evals<true>(w.counters, (restricted ? (IDENT ? 12 : 8) : 6) + dir, tap_rows);
+  if (first) count_evals<true>(w.counters, 2 + dir, t < np ? 1u : 0u);
+}
+
+// Waves per SIMD the registers are held to.  Measured on MI355X at 1024x436, per
+// pair: identity patches of FP16 records at 5 waves 6.8 ms, at 4 7.4 ms; of FP32
+// records at 5 (with spills) 16.4 ms, at 4 10.3 ms.
+constexpr int search_waves(bool fp16, bool ident) { return ident ? (fp16 ? 5 : 4) : 3; }
+
+template <int R, int C, bool FP16, bool IDENT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(search_waves(FP16, IDENT)))) void k_search(
+    DevParams P, Ws w, int colour, int iter, int slot, int mode) {
+  search_body<R, C, FP16, IDENT>(P, w, blk_here(), colour, iter, slot, mode);
+}
+
+template <int R, int C, bool FP16, bool IDENT, bool LOOP>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(search_waves(FP16, IDENT)))) void kb_search(
+    const uint8_t* __restrict__ tab, int k, BArgs A) {
+  const BatchView V = batch_view(tab, k);
+  const PairDesc* __restrict__ pd = V.pd;
+  const Item* __restrict__ it = V.it;
+  const int n = V.n, total = V.total;
+  for_each_item<true, LOOP>(it, n, total, [&](int i, Blk bk) {
+    const Item& I = it[i];
+    search_body<R, C, FP16, IDENT>(pd[I.pair].P, pd[I.pair].w, bk, A.a[0], A.a[1], A.a[2], A.a[3]);
+  });
+}
+
+// ---------------------------------------------------------------------------
+// Launchers
+// ---------------------------------------------------------------------------
+// Workgroups of one direction of a half-sweep: one per tile of the most rows
+// that still make kSearchGroups of them for both directions; smaller frames take
+// runs of pixels, down to one per lane group of a wave.
+static int search_blocks(const DevParams& P) {
+  for (int rows = 8; rows; rows >>= 1) {
+    const long long tiles = (long long)((P.W + 15) >> 4) * ((P.H + rows - 1) / rows);
+    if (2 * tiles >= kSearchGroups) return (int)tiles;
+  }
+  const int n = ((P.W + 1) >> 1) * P.H;
+  const int run = search_run((unsigned)n, n, kWave / (2 * P.r + 1));
+  return (n + run - 1) / run;
+}
+
+template <int R, int C, bool FP16>
+static hipError_t dispatch_search(const DevParams& P, const Ws& w, int colour, int iter, int slot, int mode, int ident,
+                                  hipStream_t s) {
+  const dim3 grid(search_blocks(P), 2);
+  if (ident)
+    hipLaunchKernelGGL((k_search<R, C, FP16, true>), grid, dim3(kBlock), 0, s, P, w, colour, iter, slot, mode);
+  else
+    hipLaunchKernelGGL((k_search<R, C, FP16, false>), grid, dim3(kBlock), 0, s, P, w, colour, iter, slot, mode);
+  return hipGetLastError();
+}
+
+template <int R, int C, bool FP16, bool LOOP>
+static void dispatch_search_form(bool ident, const uint8_t* tab, int k, dim3 grid, BArgs A, hipStream_t s) {
+  if (ident)
+    hipLaunchKernelGGL((kb_search<R, C, FP16, true, LOOP>), grid, dim3(kBlock), 0, s, tab, k, A);
+  else
+    hipLaunchKernelGGL((kb_search<R, C, FP16, false, LOOP>), grid, dim3(kBlock), 0, s, tab, k, A);
+}
+
+template <int R, int C, bool FP16>
+static hipError_t dispatch_search_batched(bool ident, const uint8_t* tab, int k, int grid, BArgs A, bool persist,
+                                          hipStream_t s) {
+  if (persist)
+    dispatch_search_form<R, C, FP16, true>(ident, tab, k, dim3(grid, 2), A, s);
+  else
+    dispatch_search_form<R, C, FP16, false>(ident, tab, k, dim3(grid, 2), A, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_search(const DevParams& P, const Ws& w, int colour, int iter, int slot, int mode, int ident,
+                         hipStream_t s) {
+  MSGPM_DISPATCH(dispatch_search, P, w, colour, iter, slot, mode, ident, s);
+}
+
+hipError_t launch_moments(const DevParams& P, const Ws& w, hipStream_t s) {
+  const dim3 grid(moments_blocks(P), 2), block(kBlock);
+  switch (P.r) {
+    case 1: hipLaunchKernelGGL(k_moments<1>, grid, block, 0, s, P, w); break;
+    case 2: hipLaunchKernelGGL(k_moments<2>, grid, block, 0, s, P, w); break;
+    case 3: hipLaunchKernelGGL(k_moments<3>, grid, block, 0, s, P, w); break;
+    case 4: hipLaunchKernelGGL(k_moments<4>, grid, block, 0, s, P, w); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_batched_search(int kind, const DevParams& P0, const uint8_t* tab, int k, int grid, BArgs A,
+                                 bool persist, hipStream_t s) {
+  const DevParams& P = P0;
+  if (kind == BK_MOMENTS) {
+    const dim3 g(grid, 2), block(kBlock);
+    switch (P.r) {
+      case 1: hipLaunchKernelGGL(kb_moments<1>, g, block, 0, s, tab, k); break;
+      case 2: hipLaunchKernelGGL(kb_moments<2>, g, block, 0, s, tab, k); break;
+      case 3: hipLaunchKernelGGL(kb_moments<3>, g, block, 0, s, tab, k); break;
+      case 4: hipLaunchKernelGGL(kb_moments<4>, g, block, 0, s, tab, k); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
+  MSGPM_DISPATCH(dispatch_search_batched, kind != BK_PM_RESTRICTED, tab, k, grid, A, persist, s);
+}
+
+int search_batch_blocks(int kind, const DevParams& P) {
+  return kind == BK_MOMENTS ? moments_blocks(P) : search_blocks(P);
+}
+
+}  // namespace msgpm
