@@ -1155,7 +1155,10 @@ msgpm_status msgpm_timing_read(double* ms, int64_t* launches) {
 namespace {
 
 constexpr int kCohorts = MSGPM_SERVER_MAX_COHORTS;  // cohorts in flight at most (and server streams)
-constexpr int kMaxLaunches = 4096;   // launches of one pipeline a region holds
+// Launches of one pipeline a region holds: the 4096 of the limit, beside which
+// the launches that compute moments, one per PatchMatch pass, do not count.
+constexpr int kMaxLaunches = 4096;
+constexpr int kMaxMoments = 1 + MSGPM_MAX_LEVELS;
 constexpr int kMaxLists = 48;        // distinct item lists of one pipeline
 
 struct Slot {
@@ -1177,7 +1180,7 @@ struct Cohort {
 };
 
 uint64_t region_bytes(int max_active) {
-  return align256(sizeof(BatchHead) + (uint64_t)kMaxLaunches * sizeof(LaunchTab)) +
+  return align256(sizeof(BatchHead) + (uint64_t)(kMaxLaunches + kMaxMoments) * sizeof(LaunchTab)) +
          align256((uint64_t)max_active * sizeof(PairDesc)) + align256((uint64_t)kMaxLists * max_active * sizeof(Item));
 }
 
@@ -1292,7 +1295,8 @@ msgpm_status msgpm_server_submit(msgpm_server* sv, const msgpm_params* p, const 
     delete q;
     return fail(MSGPM_E_INVALID, "NULL or misaligned buffer");
   }
-  const size_t steps = batch_schedule(q->P).size();
+  size_t steps = 0;
+  for (const BatchStep& b : batch_schedule(q->P)) steps += b.kind != BK_MOMENTS;
   if (steps > (size_t)kMaxLaunches) {
     delete q;
     return fail(MSGPM_E_UNSUPPORTED, "a served pipeline has at most %d launches (these parameters give %zu)",
