@@ -142,9 +142,55 @@ struct LaneCol {
   float fx[TG], fy[TG];
 };
 
-// Tap geometry of column dx for plane H at pixel (x, y) (H == nullptr: the
-// identity).  Returns false when the homogeneous coordinate is not positive at
-// some tap (cost = +inf); sets integral when every fraction of the column is 0.
+// Local motion of plane H around pixel (x, y): Delta(d) = (A/w - q g^T) d /
+// (1 + g.d) with q = pi(Hp), g = (h6, h7)/w; m = the 2x2 matrix by rows, then g.
+// false when the homogeneous coordinate is not positive.
+__device__ inline bool plane_motion(const double* H, int x, int y, double& qx, double& qy, float (&m)[6]) {
+  const double w = H[6] * x + H[7] * y + H[8];
+  if (!(w > 0)) return false;
+  qx = (H[0] * x + H[1] * y + H[2]) / w;
+  qy = (H[3] * x + H[4] * y + H[5]) / w;
+  const double g0 = H[6] / w, g1 = H[7] / w;
+  m[0] = (float)(H[0] / w - qx * g0);
+  m[1] = (float)(H[1] / w - qx * g1);
+  m[2] = (float)(H[3] / w - qy * g0);
+  m[3] = (float)(H[4] / w - qy * g1);
+  m[4] = (float)g0;
+  m[5] = (float)g1;
+  return true;
+}
+
+// Tap geometry of column dx under that motion.  Returns false when the
+// homogeneous coordinate is not positive at some tap (cost = +inf); sets
+// integral when every fraction of the column is 0.
+template <int R, int C>
+__device__ inline bool tap_geometry(LaneCol<R, C, false>& L, const float (&m)[6], int dx, float lim, bool& integral) {
+  L.dx = dx;
+  integral = true;
+  bool ok = true;
+  const float fdx = (float)dx;
+#pragma unroll
+  for (int t = 0; t < 2 * R + 1; ++t) {
+    const float fdy = (float)(t - R);
+    const float den = fmaf(m[5], fdy, fmaf(m[4], fdx, 1.0f));
+    ok = ok && (den > 0.f);
+    const float inv = 1.0f / den;
+    float Dx = fmaf(m[1], fdy, m[0] * fdx) * inv;
+    float Dy = fmaf(m[3], fdy, m[2] * fdx) * inv;
+    Dx = fminf(fmaxf(Dx, -lim), lim);
+    Dy = fminf(fmaxf(Dy, -lim), lim);
+    const float flx = floorf(Dx), fly = floorf(Dy);
+    // integer parts beyond +-32767 (frames are at most 32767 pixels) select
+    // the same clamped border pixel with fraction 0, so they are cut there
+    L.o[t] = pack_off((int)fminf(fmaxf(flx, -32767.f), 32767.f), (int)fminf(fmaxf(fly, -32767.f), 32767.f));
+    L.fx[t] = Dx - flx;
+    L.fy[t] = Dy - fly;
+    integral = integral && (L.fx[t] == 0.f) && (L.fy[t] == 0.f);
+  }
+  return ok;
+}
+
+// The same from plane H at pixel (x, y) (H == nullptr: the identity).
 template <int R, int C, bool IDENT>
 __device__ inline bool setup_geometry(LaneCol<R, C, IDENT>& L, const double* H, int x, int y, int dx, float lim,
                                       bool& integral) {
@@ -162,36 +208,10 @@ __device__ inline bool setup_geometry(LaneCol<R, C, IDENT>& L, const double* H, 
       }
       return true;
     }
-    // Delta(d) = (A/w - q g^T) d / (1 + g.d) with q = pi(Hp), g = (h6, h7)/w.
-    const double w = H[6] * x + H[7] * y + H[8];
-    if (!(w > 0)) return false;
-    const double qx = (H[0] * x + H[1] * y + H[2]) / w;
-    const double qy = (H[3] * x + H[4] * y + H[5]) / w;
-    const double g0 = H[6] / w, g1 = H[7] / w;
-    const float m00 = (float)(H[0] / w - qx * g0), m01 = (float)(H[1] / w - qx * g1);
-    const float m10 = (float)(H[3] / w - qy * g0), m11 = (float)(H[4] / w - qy * g1);
-    const float fg0 = (float)g0, fg1 = (float)g1;
-    bool ok = true;
-    const float fdx = (float)dx;
-#pragma unroll
-    for (int t = 0; t < 2 * R + 1; ++t) {
-      const float fdy = (float)(t - R);
-      const float den = fmaf(fg1, fdy, fmaf(fg0, fdx, 1.0f));
-      ok = ok && (den > 0.f);
-      const float inv = 1.0f / den;
-      float Dx = fmaf(m01, fdy, m00 * fdx) * inv;
-      float Dy = fmaf(m11, fdy, m10 * fdx) * inv;
-      Dx = fminf(fmaxf(Dx, -lim), lim);
-      Dy = fminf(fmaxf(Dy, -lim), lim);
-      const float flx = floorf(Dx), fly = floorf(Dy);
-      // integer parts beyond +-32767 (frames are at most 32767 pixels) select
-      // the same clamped border pixel with fraction 0, so they are cut there
-      L.o[t] = pack_off((int)fminf(fmaxf(flx, -32767.f), 32767.f), (int)fminf(fmaxf(fly, -32767.f), 32767.f));
-      L.fx[t] = Dx - flx;
-      L.fy[t] = Dy - fly;
-      integral = integral && (L.fx[t] == 0.f) && (L.fy[t] == 0.f);
-    }
-    return ok;
+    double qx, qy;
+    float m[6];
+    if (!plane_motion(H, x, y, qx, qy, m)) return false;
+    return tap_geometry(L, m, dx, lim, integral);
   }
 }
 

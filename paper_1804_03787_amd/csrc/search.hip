@@ -53,19 +53,28 @@ constexpr unsigned kRefresh = 1u << 31;  // in a candidate mask: the current cos
 constexpr int kSlots = 64;  // pixels of a workgroup
 
 struct SearchLds {
-  int tgt[kTgtRows][kSlots];  // candidate targets x | y << 16
-  int pix[kSlots];            // x | y << 16
-  int best0[kSlots], best1[kSlots];  // best target before the half-sweep, after propagation
-  int best[kSlots];           // best target
+  int tgt[kTgtRows][kSlots];  // random search: drawn offsets, then targets x | y << 16
+  int ptgt[5][kSlots];        // propagation (and plane) targets
+  uint16_t lb[kTgtRows][kSlots], plb[5][kSlots];  // their cost bounds (upper half of an FP32)
+  unsigned mask[2][kSlots];   // candidates to evaluate, propagation and random search
+  unsigned key[2][kSlots];    // the one of the lowest bound (its number in the low 4 bits)
+  int pix[kSlots];            // x | y << 16, -1: no pixel
+  int best0[kSlots], best[kSlots];  // best target before the half-sweep and now
   float bc[kSlots];           // its cost
-  unsigned mask[kSlots];      // candidates to evaluate
-  unsigned key[kSlots];       // the candidate of the lowest bound (its number in the low 4 bits)
-  unsigned memo[kSlots];      // tried positions around the best
-  float shift[kSlots];        // of the distortion bound
+  unsigned memo[kSlots];      // positions tried around best0 before
+  unsigned tried[kSlots];     // positions tried around the best after propagation
+  int won[kSlots];            // random search changed the best
+  uint32_t src[3][kSlots];    // the pixel's moments
+  float shift[kSlots];        // distorted patches: of the bound, and the plane's local motion
+  float motion[6][kSlots];
   int order[kSlots];          // pixels with work, most candidates first
-  int n;                      // pixels, then pixels with work
-  uint16_t lb[kTgtRows][kSlots];  // candidates' cost bounds (upper half of an FP32)
 };
+
+__device__ inline void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 __device__ inline int pack_xy(int x, int y) { return x | (y << 16); }
 __device__ inline int xy_x(int v) { return v & 0xffff; }
@@ -280,11 +289,7 @@ __device__ inline Moments moments_buf(const Ws& w, int f, int n) {
 __device__ inline int dot4(uint32_t a, uint32_t b, int c) {
   return __builtin_amdgcn_sdot4((int)a, (int)b, c, false);
 }
-// Squared distance of two pixels' moments (the last byte is not one).
-__device__ inline int moments_norm2(u32x3 a) {
-  const uint32_t z = a.z & 0xffffffu;
-  return dot4(a.x, a.x, dot4(a.y, a.y, dot4(z, z, 0)));
-}
+__device__ inline int moments_norm2(u32x3 a) { return dot4(a.x, a.x, dot4(a.y, a.y, dot4(a.z, a.z, 0))); }
 
 // ---------------------------------------------------------------------------
 // Half-sweep
@@ -293,59 +298,44 @@ __device__ inline int moments_norm2(u32x3 a) {
 // What bounds the costs of a pixel's candidates.
 struct Bound {
   u32x3 src;    // the pixel's moments, without the last byte
-  int src2;     // their squared norm
-  float shift;  // b of the pixel's distortion, in units of kRough; infinite: no bound
+  float shift;  // b of the pixel's distortion times kRough; infinite: no bound
   float unit2;  // squared length of a unit, less what the cost may be under the exact SSD
 };
 
-// Largest |a(d)| / |d| of the distortion of plane H at (x, y), a(d) = Delta(d) - d
-// with Delta(d) = M d / (1 + g d): (|M - I| + |g| |d|) / (1 - |g| |d|) in the
-// spectral norm, |d| at most sqrt(2) r; infinite where that leaves |a| <= 1.
-__device__ inline float distortion(const double* H, int x, int y, int r) {
-  const double w = H[6] * x + H[7] * y + H[8];
+// Largest |a(d)| / |d| of a distortion, a(d) = Delta(d) - d with Delta(d) = M d /
+// (1 + g d): (|M - I| + |g| |d|) / (1 - |g| |d|) in the spectral norm, |d| at
+// most sqrt(2) r; infinite where that does not keep |a| <= 1.
+__device__ inline float distortion(const float (&m)[6], int r) {
   const float inf = __builtin_huge_valf();
-  if (!(w > 0)) return inf;
-  const double qx = (H[0] * x + H[1] * y + H[2]) / w, qy = (H[3] * x + H[4] * y + H[5]) / w;
-  const double g0 = H[6] / w, g1 = H[7] / w;
-  const float a = (float)(H[0] / w - qx * g0 - 1.0), b = (float)(H[1] / w - qx * g1);
-  const float c = (float)(H[3] / w - qy * g0), d = (float)(H[4] / w - qy * g1 - 1.0);
+  const float a = m[0] - 1.f, b = m[1], c = m[2], d = m[3] - 1.f;
   const float s = fmaf(a, a, b * b) + fmaf(c, c, d * d), det = a * d - b * c;
   const float norm = sqrtf(0.5f * (s + sqrtf(fmaxf(s * s - 4.f * det * det, 0.f))));
-  const float reach = 1.4143f * (float)r, g = sqrtf((float)(g0 * g0 + g1 * g1)) * reach;
+  const float reach = 1.4143f * (float)r, g = sqrtf(fmaf(m[4], m[4], m[5] * m[5])) * reach;
   if (!(g < 0.5f)) return inf;
   const float v = (norm + g) / (1.f - g) * 1.001f + 1e-4f;
   return v * reach < 1.f ? v : inf;
 }
 
-__device__ inline Bound make_bound(const Moments& M1, int p, float shift, float scale) {
-  Bound f;
-  f.src = M1.at(p);
-  f.src.z &= 0xffffffu;
-  f.src2 = moments_norm2(f.src);
-  f.shift = shift * kRough;
-  f.unit2 = scale > 0.f ? 0.9999f / (scale * scale) : 0.f;
-  return f;
-}
+__device__ inline float bound_unit2(float scale) { return scale > 0.f ? 0.9999f / (scale * scale) : 0.f; }
 
 // A cost that target p's cannot be below, or 0.
 __device__ inline float cost_bound(const Bound& f, const Moments& M2, int p) {
-  const u32x3 t = M2.at(p);
-  const int dot = dot4(f.src.x, t.x, dot4(f.src.y, t.y, dot4(f.src.z, t.z, 0)));
-  const float d = sqrtf((float)(f.src2 + moments_norm2(t) - 2 * dot));
+  u32x3 t = M2.at(p);
   const uint32_t rough = t.z >> 24;
+  t.z &= 0xffffffu;
+  const int dot = dot4(f.src.x, t.x, dot4(f.src.y, t.y, dot4(f.src.z, t.z, 0)));
+  const float d = sqrtf((float)(moments_norm2(f.src) + moments_norm2(t) - 2 * dot));
   const float less = f.shift > 0.f ? f.shift * (rough == 255u ? __builtin_huge_valf() : (float)rough) : 0.f;
   const float v = d - kMomSlack - less;
   return v > 0.f ? v * v * f.unit2 : 0.f;  // less infinite or not a number: 0
 }
 
-// Random-search target k of pixel p around target (bx, by).
-__device__ inline void draw_target(const DevParams& P, int p, int bx, int by, int k, int iter, uint64_t w3, int& tx,
-                                   int& ty) {
+// Random-search offset k of pixel p.
+__device__ inline int32_t draw_offset(const DevParams& P, int p, int k, int iter, uint64_t w3) {
   const int Rk = P.R0 >> k;
   uint64_t c[4] = {(uint64_t)(uint32_t)p, (uint64_t)k, (uint64_t)iter, w3};
   philox4x64(c, P.seed, 0);
-  tx = clampi(bx + draw_below(c[0], (uint32_t)(2 * Rk + 1)) - Rk, 0, P.W - 1);
-  ty = clampi(by + draw_below(c[1], (uint32_t)(2 * Rk + 1)) - Rk, 0, P.H - 1);
+  return pack_off(draw_below(c[0], (uint32_t)(2 * Rk + 1)) - Rk, draw_below(c[1], (uint32_t)(2 * Rk + 1)) - Rk);
 }
 
 // The bit of target (tx, ty) among the tried positions around (bx, by), 0 if outside.
@@ -360,17 +350,36 @@ constexpr unsigned kTriedCentre = 1u << 12;
 __device__ inline uint16_t bound_bits(float v) { return (uint16_t)(__float_as_uint(v) >> 16); }
 __device__ inline unsigned bound_key(float v, int k) { return (__float_as_uint(v) & ~15u) | (unsigned)k; }
 
-// Evaluates the candidates of the n listed pixels, one pixel per lane group at a
-// time, the waves taking the list in turn; rows: tap rows computed (counted at
-// the group's last lane).
+// Lists the pixels with work in S.order, most candidates (at most `most`) first;
+// returns their number.  Every wave makes the same list for itself.
+__device__ inline int sort_by_work(SearchLds& S, int phase, int most) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int cnt = __popc(S.mask[phase][lane]);
+  const unsigned long long lt = (1ull << lane) - 1ull;
+  int n = 0;
+  for (int c = most; c > 0; --c) {
+    const unsigned long long m = __ballot(cnt == c);
+    if (cnt == c) S.order[n + __popcll(m & lt)] = lane;
+    n += __popcll(m);
+  }
+  wave_lds_fence();
+  return n;
+}
+
+// Evaluates the candidates of a phase, one pixel per lane group at a time, the
+// waves taking the list of pixels with work in turn; rows: tap rows computed
+// (counted at the group's last lane).
 template <int R, int C, bool FP16, bool IDENT>
-__device__ inline void evaluate(const DevParams& P, const Ws& w, int dir, SearchLds& S, int n, unsigned& rows_out) {
+__device__ inline void evaluate(const DevParams& P, const Ws& w, int dir, SearchLds& S, int phase, unsigned& rows_out) {
   constexpr int G = 2 * R + 1, NG = kWave / G;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / G, j = lane - g * G, base = g * G;
   const int W = P.W, H = P.H;
   const float gw = P.gw;
   const Feat F1 = feat_buf<C, FP16>(w.feat[dir], W, H), F2 = feat_buf<C, FP16>(w.feat[1 - dir], W, H);
+  const int(*tgt)[kSlots] = phase ? S.tgt : S.ptgt;
+  const uint16_t(*lbs)[kSlots] = phase ? S.lb : S.plb;
+  const int n = sort_by_work(S, phase, phase ? P.nk : 6);
   for (int i0 = wave * NG; i0 < n; i0 += NG * (kBlock / kWave)) {
     const int i = i0 + g;
     if (g >= NG || i >= n) continue;
@@ -379,16 +388,17 @@ __device__ inline void evaluate(const DevParams& P, const Ws& w, int dir, Search
     const int x = xy_x(pix), y = xy_y(pix);
     int best = S.best[sl], kbest = -1;
     float bc = S.bc[sl];
-    unsigned m = S.mask[sl], rows = 0;
-    const unsigned key = S.key[sl];
+    unsigned m = S.mask[phase][sl], rows = 0;
     LaneCol<R, C, IDENT> L;
     int geo = 1;
     if constexpr (IDENT) {
       L.dx = j - R;
     } else {
-      const double* Hp = plane_H(w, w.hlabel[dir][y * W + x]);
-      bool integral;
-      const bool ok = setup_geometry<R, C, false>(L, Hp, x, y, j - R, 4.0f * (float)(W > H ? W : H), integral);
+      float mo[6];
+#pragma unroll
+      for (int q = 0; q < 6; ++q) mo[q] = S.motion[q][sl];
+      bool integral = false, ok = S.shift[sl] >= 0.f;
+      if (ok) ok = tap_geometry<R, C>(L, mo, j - R, 4.0f * (float)(W > H ? W : H), integral);
       geo = group_geometry<G>(ok, integral, base);
     }
     // geo 2: a homogeneous coordinate is not positive, every cost is +inf
@@ -406,12 +416,12 @@ __device__ inline void evaluate(const DevParams& P, const Ws& w, int dir, Search
     m &= geo == 2 ? 0u : ~kRefresh;
     // the candidate of the lowest bound, then the others in order.  A cost equal
     // to the best one wins only before the candidate that holds it.
-    int k = (int)(key & 15u);
+    int k = (int)(S.key[phase][sl] & 15u);
     while (m) {
       if (!((m >> k) & 1u)) k = __builtin_ctz(m);
       m &= ~(1u << k);
-      const int t = S.tgt[k][sl];
-      const float lb = __uint_as_float((unsigned)S.lb[k][sl] << 16);
+      const int t = tgt[k][sl];
+      const float lb = __uint_as_float((unsigned)lbs[k][sl] << 16);
       const float top = k < kbest ? __uint_as_float(__float_as_uint(bc) + 1u) : bc;
       bool won;
       float c = 0.f;
@@ -445,113 +455,136 @@ __device__ inline void evaluate(const DevParams& P, const Ws& w, int dir, Search
     if (j == G - 1) {
       S.best[sl] = best;
       S.bc[sl] = bc;
+      if (phase) S.won[sl] = kbest >= 0;
       rows_out += rows;
     }
   }
 }
 
-// Lists the np pixels with work in S.order, most candidates first, and puts their
-// number in S.n; called by one wave.
-__device__ inline void sort_by_work(SearchLds& S, int np) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int cnt = lane < np ? __popc(S.mask[lane]) : 0;
-  const unsigned long long lt = (1ull << lane) - 1ull;
-  int n = 0;
-  for (int c = kTgtRows; c > 0; --c) {
-    const unsigned long long m = __ballot(cnt == c);
-    if (cnt == c) S.order[n + __popcll(m & lt)] = lane;
-    n += __popcll(m);
-  }
-  if (lane == 0) S.n = n;
-}
-
-// Adds candidate k at target (tx, ty) of slot sl with cost bound lb.
-__device__ inline void add_candidate(SearchLds& S, int sl, int k, int tx, int ty, float lb) {
-  S.tgt[k][sl] = pack_xy(tx, ty);
-  S.lb[k][sl] = bound_bits(lb);
-  atomicMin(&S.key[sl], bound_key(lb, k));
-  atomicOr(&S.mask[sl], 1u << k);
-}
-
-// State of slot sl's pixel before propagation.
-template <int R, bool IDENT>
-__device__ inline void open_slot(const DevParams& P, const Ws& w, int dir, SearchLds& S, int sl, int x, int y,
-                                 bool first) {
-  const int p = y * P.W + x;
-  const int32_t v = w.nnf[dir][p];
-  const int best = pack_xy(x + off_dx(v), y + off_dy(v));
-  S.pix[sl] = pack_xy(x, y);
-  S.best0[sl] = best;
-  S.best[sl] = best;
-  S.bc[sl] = first ? 0.f : w.cost[dir][p];
-  S.memo[sl] = first ? 0u : (unsigned)w.win[dir][p] & kMemoTried;
-  S.mask[sl] = first ? kRefresh : 0u;
-  S.key[sl] = ~0u;
-  if constexpr (!IDENT) S.shift[sl] = distortion(plane_H(w, w.hlabel[dir][p]), x, y, R);
-}
-
-// Candidate k of propagation: the neighbours' offsets (left, right, up, down), then
-// (distorted patches) the target where the region plane sends the pixel, rounded
-// to the grid.
-template <bool IDENT>
-__device__ inline void offer_neighbour(const DevParams& P, const Ws& w, int dir, SearchLds& S, int sl, int k,
-                                       bool first, const Moments& M1, const Moments& M2, float scale,
-                                       unsigned& evals) {
-  const int W = P.W, H = P.H, pix = S.pix[sl], x = xy_x(pix), y = xy_y(pix), p = y * W + x;
-  int tx, ty;
-  bool need = true;
-  if (IDENT || k < 4) {
-    const int nx = x + (k == 0 ? -1 : (k == 1 ? 1 : 0));
-    const int ny = y + (k == 2 ? -1 : (k == 3 ? 1 : 0));
-    if (nx < 0 || nx >= W || ny < 0 || ny >= H) return;
-    const int q = ny * W + nx;
-    const int32_t v = w.nnf[dir][q];
-    tx = clampi(x + off_dx(v), 0, W - 1);
-    ty = clampi(y + off_dy(v), 0, H - 1);
-    if (!first) {
-      const int m = w.win[dir][q];
-      need = m < 0 && (m & (int)kMemoChanged);
+// Which pixel slot i of workgroup b has.
+struct SlotMap {
+  const int32_t* list;   // restricted: the list of pixels, from its front or its back
+  int step;              // its direction
+  int rows, ntx;         // tiles: rows of one, tiles per row of the frame
+  int run, colour, W, H;
+  unsigned b, cnt;
+  __device__ inline bool at(int i, int& x, int& y) const {
+    if (rows) {
+      y = (int)(b / ntx) * rows + (i >> 3);
+      x = (int)(b % ntx) * 16 + 2 * (i & 7) + ((y + colour) & 1);
+      return x < W && y < H;
     }
-  } else {
-    const double* Hp = plane_H(w, w.hlabel[dir][p]);
-    const double ww = Hp[6] * x + Hp[7] * y + Hp[8];
-    if (!(ww > 0)) return;
-    const double qx = (Hp[0] * x + Hp[1] * y + Hp[2]) / ww;
-    const double qy = (Hp[3] * x + Hp[4] * y + Hp[5]) / ww;
-    const double dl = (double)(4.0f * (float)(W > H ? W : H));
-    double rx = floor(qx + 0.5), ry = floor(qy + 0.5);
-    rx = rx < -dl ? -dl : (rx > dl ? dl : rx);
-    ry = ry < -dl ? -dl : (ry > dl ? dl : ry);
-    tx = clampi((int)rx, 0, W - 1);
-    ty = clampi((int)ry, 0, H - 1);
-    need = first;
+    const unsigned q = b * run + i;
+    if (q >= cnt) return false;
+    if (list) {
+      const int p = list[(long long)step * (int)q];
+      y = p / W;
+      x = p - y * W;
+      return true;
+    }
+    const int Wh = (W + 1) >> 1;
+    y = (int)(q / Wh);
+    x = 2 * (int)(q - (unsigned)y * Wh) + ((y + colour) & 1);
+    return x < W;
   }
-  if (pack_xy(tx, ty) == S.best0[sl]) return;
-  ++evals;
-  if (!need) return;
-  // the bounds drop few of these candidates but in the first half-sweep, where
-  // the best may still be a random one
-  float lb = 0.f;
-  if (first) lb = cost_bound(make_bound(M1, p, IDENT ? 0.f : S.shift[sl], scale), M2, ty * W + tx);
-  add_candidate(S, sl, k, tx, ty, lb);
+};
+
+// Opens slot sl and offers neighbour k's offset (0 left, 1 right, 2 up, 3 down);
+// the lanes of k == 0 also load the pixel's own state.
+template <int R, bool IDENT>
+__device__ inline void open_slot(const DevParams& P, const Ws& w, int dir, SearchLds& S, const SlotMap& M, int sl, int k,
+                                 bool first, const Moments& M1, const Moments& M2, float unit2, unsigned& evals) {
+  const int W = P.W, H = P.H;
+  int x, y;
+  if (!M.at(sl, x, y)) {
+    if (k == 0) S.pix[sl] = -1;
+    return;
+  }
+  const int p = y * W + x;
+  const int nx = x + (k == 0 ? -1 : (k == 1 ? 1 : 0));
+  const int ny = y + (k == 2 ? -1 : (k == 3 ? 1 : 0));
+  const bool inside = nx >= 0 && nx < W && ny >= 0 && ny < H;
+  const int q = inside ? ny * W + nx : p;
+  const int32_t v0 = w.nnf[dir][p], v = w.nnf[dir][q];
+  const int wq = w.win[dir][q];
+  Bound f{};
+  if (k == 0 || first) f.src = M1.at(p);
+  f.unit2 = unit2;
+  const int best0 = pack_xy(x + off_dx(v0), y + off_dy(v0));
+  int tp = -1;
+  if (k == 0) {
+    S.pix[sl] = pack_xy(x, y);
+    S.best0[sl] = best0;
+    S.best[sl] = best0;
+    S.bc[sl] = first ? 0.f : w.cost[dir][p];
+    S.memo[sl] = first ? 0u : (unsigned)w.win[dir][p] & kMemoTried;
+    S.won[sl] = 0;
+    S.src[0][sl] = f.src.x;
+    S.src[1][sl] = f.src.y;
+    S.src[2][sl] = f.src.z & 0xffffffu;
+  }
+  f.src.z &= 0xffffffu;
+  if constexpr (!IDENT) {
+    // shift: negative where the plane has no motion (no cost is finite)
+    if (k == 0 || first) {
+      double qx, qy;
+      float m[6] = {};
+      f.shift = -1.f;
+      if (plane_motion(plane_H(w, w.hlabel[dir][p]), x, y, qx, qy, m)) {
+        f.shift = distortion(m, R) * kRough;
+        // plane candidate: where the region plane sends the pixel, rounded to the grid
+        const double dl = (double)(4.0f * (float)(W > H ? W : H));
+        double rx = floor(qx + 0.5), ry = floor(qy + 0.5);
+        rx = rx < -dl ? -dl : (rx > dl ? dl : rx);
+        ry = ry < -dl ? -dl : (ry > dl ? dl : ry);
+        tp = pack_xy(clampi((int)rx, 0, W - 1), clampi((int)ry, 0, H - 1));
+      }
+      if (k == 0) {
+        S.shift[sl] = f.shift;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) S.motion[i][sl] = m[i];
+      }
+    }
+  }
+  auto offer = [&](int kk, int t, bool need) {
+    if (t == best0) return;
+    ++evals;
+    if (!need) return;
+    // the bounds drop few of these candidates but in the first half-sweep,
+    // where the best may still be a random one
+    const float lb = first ? cost_bound(f, M2, xy_y(t) * W + xy_x(t)) : 0.f;
+    S.ptgt[kk][sl] = t;
+    S.plb[kk][sl] = bound_bits(lb);
+    atomicMin(&S.key[0][sl], bound_key(lb, kk));
+    atomicOr(&S.mask[0][sl], 1u << kk);
+  };
+  if (inside)
+    offer(k, pack_xy(clampi(x + off_dx(v), 0, W - 1), clampi(y + off_dy(v), 0, H - 1)),
+          first || (wq < 0 && (wq & (int)kMemoChanged)));
+  if (!IDENT && k == 0 && tp != -1) offer(4, tp, first);
+  if (k == 0 && first) atomicOr(&S.mask[0][sl], kRefresh);
 }
 
-// Candidate k of random search, around the best after propagation.
+// Random-search candidate k of slot sl, around the best after propagation.
 template <bool IDENT>
-__device__ inline void offer_random(const DevParams& P, SearchLds& S, int sl, int k, int iter, uint64_t w3,
-                                    const Moments& M1, const Moments& M2, float scale, unsigned& evals) {
-  const int W = P.W, pix = S.pix[sl], p = xy_y(pix) * W + xy_x(pix);
+__device__ inline void offer_random(const DevParams& P, SearchLds& S, int sl, int k, const Moments& M2, float unit2,
+                                    unsigned& evals) {
+  if (S.pix[sl] < 0) return;
   const int b = S.best[sl], bx = xy_x(b), by = xy_y(b);
-  int tx, ty;
-  draw_target(P, p, bx, by, k, iter, w3, tx, ty);
+  const int32_t v = S.tgt[k][sl];
+  const int tx = clampi(bx + off_dx(v), 0, P.W - 1), ty = clampi(by + off_dy(v), 0, P.H - 1);
   const unsigned bit = tried_bit(tx, ty, bx, by);
   if (bit == kTriedCentre) return;
   ++evals;
   // of lanes that draw one position together, the first to note it keeps it
-  if (bit && (atomicOr(&S.memo[sl], bit) & bit)) return;
-  const float lb = cost_bound(make_bound(M1, p, IDENT ? 0.f : S.shift[sl], scale), M2, ty * W + tx);
+  if (bit && ((atomicOr(&S.tried[sl], bit) | (b == S.best0[sl] ? S.memo[sl] : 0u)) & bit)) return;
+  const Bound f{u32x3{S.src[0][sl], S.src[1][sl], S.src[2][sl]}, IDENT ? 0.f : S.shift[sl], unit2};
+  const float lb = cost_bound(f, M2, ty * P.W + tx);
   if (lb >= S.bc[sl]) return;
-  add_candidate(S, sl, k, tx, ty, lb);
+  S.tgt[k][sl] = pack_xy(tx, ty);
+  S.lb[k][sl] = bound_bits(lb);
+  atomicMin(&S.key[1][sl], bound_key(lb, k));
+  atomicOr(&S.mask[1][sl], 1u << k);
 }
 
 // Calls f(slot, k) for every slot < np and k < nk, the lanes of the workgroup
@@ -586,83 +619,66 @@ __device__ __forceinline__ void search_body(const DevParams& P, const Ws& w, Blk
                                             int mode) {
   constexpr int G = 2 * R + 1, NG = kWave / G;
   __shared__ SearchLds S;
-  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+  const int t = threadIdx.x;
   const int dir = bk.y;
-  const int W = P.W, H = P.H, Wh = (W + 1) >> 1;
+  const int W = P.W, H = P.H;
   const bool restricted = (mode & SM_RESTRICTED) != 0, first = (mode & SM_FIRST) != 0;
-  const unsigned cap = (unsigned)Wh * (unsigned)H;
-  const unsigned cnt = restricted ? w.act_count[2 * (2 * dir + colour) + (IDENT ? 1 : 0)] : cap;
-  const int rows = restricted ? 0 : tile_rows(W, H, bk.nx);
-  const int run = rows ? 8 * rows : search_run(cnt, bk.nx, NG);
-  const int nb = rows ? bk.nx : (int)((cnt + run - 1) / run);
+  const unsigned cap = (unsigned)((W + 1) >> 1) * (unsigned)H;
+  SlotMap M;
+  M.cnt = restricted ? w.act_count[2 * (2 * dir + colour) + (IDENT ? 1 : 0)] : cap;
+  M.list = restricted ? w.act[2 * dir + colour] + (IDENT ? cap - 1u : 0u) : nullptr;
+  M.step = IDENT ? -1 : 1;
+  M.rows = restricted ? 0 : tile_rows(W, H, bk.nx);
+  M.ntx = (W + 15) >> 4;
+  M.run = M.rows ? 8 * M.rows : search_run(M.cnt, bk.nx, NG);
+  M.colour = colour;
+  M.W = W;
+  M.H = H;
+  const int nb = M.rows ? bk.nx : (int)((M.cnt + M.run - 1) / M.run), np = M.run;
   if (bk.x >= nb) return;
-  if (wave == 0) {
-    const unsigned b = (unsigned)xcd_remap(bk.x, nb), i = b * run + lane;
-    int x, y;
-    bool act = lane < run;
-    if (rows) {
-      const int ntx = (W + 15) >> 4;
-      y = (int)(b / ntx) * rows + (lane >> 3);
-      x = (int)(b % ntx) * 16 + 2 * (lane & 7) + ((y + colour) & 1);
-      act = act && x < W && y < H;
-    } else if (restricted) {
-      act = act && i < cnt;
-      const int q = act ? w.act[2 * dir + colour][IDENT ? cap - 1u - i : i] : 0;
-      y = q / W;
-      x = q - y * W;
-    } else {
-      y = (int)(i / Wh);
-      x = 2 * (int)(i - (unsigned)y * Wh) + ((y + colour) & 1);
-      act = act && i < cap && x < W;
-    }
-    const unsigned long long on = __ballot(act);
-    if (act) open_slot<R, IDENT>(P, w, dir, S, __popcll(on & ((1ull << lane) - 1ull)), x, y, first);
-    if (lane == 0) S.n = __popcll(on);
-  }
-  __syncthreads();
-  const int np = S.n;
-  const float scale = __uint_as_float(w.act_count[8]);
+  M.b = xcd_remap(bk.x, nb);
+  const float unit2 = bound_unit2(__uint_as_float(w.act_count[8]));
   const Moments M1 = moments_buf(w, dir, W * H), M2 = moments_buf(w, 1 - dir, W * H);
   const uint64_t w3 = rng_word3(2, dir, slot, 0);
   unsigned evals = 0, tap_rows = 0;
+  if (t < kSlots) {
+    S.mask[0][t] = S.mask[1][t] = 0u;
+    S.key[0][t] = S.key[1][t] = ~0u;
+    S.tried[t] = 0u;
+    S.pix[t] = -1;
+  }
+  __syncthreads();
+  // the neighbours' candidates, and the draws while their loads are on the way
+  each_candidate(np, 4, [&](int sl, int k) {
+    open_slot<R, IDENT>(P, w, dir, S, M, sl, k, first, M1, M2, unit2, evals);
+  });
+  each_candidate(np, P.nk, [&](int sl, int k) {
+    int x, y;
+    if (M.at(sl, x, y)) S.tgt[k][sl] = draw_offset(P, y * W + x, k, iter, w3);
+  });
+  __syncthreads();
 #pragma unroll 1
-  for (int random = 0; random < 2; ++random) {
-    if (!random)
-      each_candidate(np, IDENT ? 4 : 5, [&](int sl, int k) {
-        offer_neighbour<IDENT>(P, w, dir, S, sl, k, first, M1, M2, scale, evals);
-      });
-    else
-      each_candidate(np, P.nk, [&](int sl, int k) {
-        offer_random<IDENT>(P, S, sl, k, iter, w3, M1, M2, scale, evals);
-      });
-    __syncthreads();
-    if (wave == 0) sort_by_work(S, np);
-    __syncthreads();
-    evaluate<R, C, FP16, IDENT>(P, w, dir, S, S.n, tap_rows);
-    __syncthreads();
-    if (!random) {
-      if (t < np) {
-        const int best = S.best[t];
-        S.best1[t] = best;
-        if (best != S.best0[t]) S.memo[t] = 0;
-        S.mask[t] = 0;
-        S.key[t] = ~0u;
-      }
+  for (int phase = 0; phase < 2; ++phase) {
+    if (phase) {
+      each_candidate(np, P.nk, [&](int sl, int k) { offer_random<IDENT>(P, S, sl, k, M2, unit2, evals); });
       __syncthreads();
     }
+    evaluate<R, C, FP16, IDENT>(P, w, dir, S, phase, tap_rows);
+    __syncthreads();
   }
-  if (t < np) {
-    const int pix = S.pix[t], x = xy_x(pix), y = xy_y(pix), p = y * W + x;
-    const int best = S.best[t];
-    const bool changed = best != S.best0[t];
+  const int pix = t < kSlots ? S.pix[t] : -1;
+  if (pix >= 0) {
+    const int x = xy_x(pix), y = xy_y(pix), p = y * W + x;
+    const int best = S.best[t], best0 = S.best0[t];
+    const bool changed = best != best0;
     if (changed) w.nnf[dir][p] = pack_off(xy_x(best) - x, xy_y(best) - y);
     if (changed || first) w.cost[dir][p] = S.bc[t];
-    const unsigned tried = best == S.best1[t] ? S.memo[t] : 0u;
+    const unsigned tried = S.won[t] ? 0u : S.tried[t] | (changed ? 0u : S.memo[t]);
     w.win[dir][p] = mode & SM_LAST ? -1 : (int)(kMemoSign | (changed ? kMemoChanged : 0u) | tried);
   }
   count_evals<true>(w.counters, (restricted ? (IDENT ? 10 : 4) : 0) + dir, evals);
   count_evals<true>(w.counters, (restricted ? (IDENT ? 12 : 8) : 6) + dir, tap_rows);
-  if (first) count_evals<true>(w.counters, 2 + dir, t < np ? 1u : 0u);
+  if (first) count_evals<true>(w.counters, 2 + dir, pix >= 0 ? 1u : 0u);
 }
 
 // Waves per SIMD the registers are held to.  Measured on MI355X at 1024x436, per
