@@ -209,37 +209,143 @@ __device__ inline bool denormalise(const double (&h)[8], double s1, double c1x, 
   return true;
 }
 
-// Normalised 4-point DLT with H[8] = 1.
+// Partial pivoting on rows k .. N-1 of column `col`: exchanges row k with the
+// first largest; false if that is below 1e-10.
+template <int N, int M>
+__device__ inline bool pivot_rows(double (&A)[N][M], int k, int col) {
+  int piv = k;
+  double best = fabs(A[k][col]);
+#pragma unroll
+  for (int i = k + 1; i < N; ++i) {
+    const double a = fabs(A[i][col]);
+    if (a > best) {
+      best = a;
+      piv = i;
+    }
+  }
+  if (best < 1e-10) return false;
+#pragma unroll
+  for (int i = k + 1; i < N; ++i) {
+    const bool sw = (i == piv);
+#pragma unroll
+    for (int j = col; j < M; ++j) {
+      const double t = A[k][j];
+      A[k][j] = sw ? A[i][j] : A[k][j];
+      A[i][j] = sw ? t : A[i][j];
+    }
+  }
+  return true;
+}
+
+template <int N, int M>
+__device__ inline void eliminate_rows(double (&A)[N][M], int k, int col) {
+#pragma unroll
+  for (int i = k + 1; i < N; ++i) {
+    const double f = A[i][col] / A[k][col];
+#pragma unroll
+    for (int j = col; j < M; ++j) A[i][j] -= f * A[k][j];
+  }
+}
+
+// Normalised 4-point DLT with H[8] = 1: the result of gauss8 on the rows
+//   2i   (x y 1  0 0 0  -xu -yu | u)      2i+1  (0 0 0  x y 1  -xv -yv | v)
+// without its structural zeros.  The first three columns concern the even rows
+// only (an odd row's factor there is a zero), the next three the odd rows, and
+// what is left is a 2x2 system in the last two, so that the elimination takes 4
+// rows of 6 values and then 5 of 6 instead of 8 of 9, with 16 divisions instead
+// of 28 and a third of the exchanges.  Row exchanges decide which of two equally
+// large pivots comes first, so the odd rows are taken up in the order gauss8's
+// exchanges leave them in: 1 3 5 7, the pivot of the second column sending row 1
+// to its own place (row 2, 4 or 6), and if that is row 2, the pivot of the third
+// column sending it on to its place.  A zero may have another sign than with
+// the structural zeros carried along; denormalise's sums, which start from +0,
+// cannot tell.  The eliminations of 256 hypotheses per window were a third of
+// RANSAC: 3.05 -> 2.80 ms per 1024x436 pair, 15.6 -> 14.8 ms at 2048x872 (52
+// instead of 208 bytes of scratch per lane).
 __device__ inline bool dlt4(const double (&sx)[4], const double (&sy)[4], const double (&dx)[4],
                             const double (&dy)[4], double* Hout) {
   double s1, c1x, c1y, s2, c2x, c2y;
   if (!hartley_n<4>(sx, sy, s1, c1x, c1y)) return false;
   if (!hartley_n<4>(dx, dy, s2, c2x, c2y)) return false;
-  double A[8][8], b[8], h[8];
+  double E[4][6];  // even rows: columns 0 1 2 6 7, right-hand side
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const double x = s1 * (sx[i] - c1x), y = s1 * (sy[i] - c1y);
-    const double u = s2 * (dx[i] - c2x), v = s2 * (dy[i] - c2y);
-    A[2 * i][0] = x;
-    A[2 * i][1] = y;
-    A[2 * i][2] = 1;
-    A[2 * i][3] = 0;
-    A[2 * i][4] = 0;
-    A[2 * i][5] = 0;
-    A[2 * i][6] = -x * u;
-    A[2 * i][7] = -y * u;
-    A[2 * i + 1][0] = 0;
-    A[2 * i + 1][1] = 0;
-    A[2 * i + 1][2] = 0;
-    A[2 * i + 1][3] = x;
-    A[2 * i + 1][4] = y;
-    A[2 * i + 1][5] = 1;
-    A[2 * i + 1][6] = -x * v;
-    A[2 * i + 1][7] = -y * v;
-    b[2 * i] = u;
-    b[2 * i + 1] = v;
+    const double x = s1 * (sx[i] - c1x), y = s1 * (sy[i] - c1y), u = s2 * (dx[i] - c2x);
+    E[i][0] = x;
+    E[i][1] = y;
+    E[i][2] = 1;
+    E[i][3] = -x * u;
+    E[i][4] = -y * u;
+    E[i][5] = u;
   }
-  if (!gauss8(A, b, h)) return false;
+  if (!pivot_rows(E, 0, 0)) return false;
+  eliminate_rows(E, 0, 0);
+  // where the second column's pivot stands: row 2, 4 or 6 (E[1..3])
+  int at = 1;
+  {
+    double best = fabs(E[1][1]);
+#pragma unroll
+    for (int i = 2; i < 4; ++i)
+      if (fabs(E[i][1]) > best) {
+        best = fabs(E[i][1]);
+        at = i;
+      }
+    if (best < 1e-10) return false;
+  }
+  // it is exchanged with row 1, so the even rows left keep their order
+  double F[3][5];  // pivot of column 1, then the two even rows left; columns 1 2 6 7, rhs
+#pragma unroll
+  for (int j = 1; j < 6; ++j) {
+    F[0][j - 1] = at == 1 ? E[1][j] : (at == 2 ? E[2][j] : E[3][j]);
+    F[1][j - 1] = at == 1 ? E[2][j] : E[1][j];
+    F[2][j - 1] = at == 3 ? E[2][j] : E[3][j];
+  }
+  eliminate_rows(F, 0, 0);
+  // column 2: the later row wins only if strictly larger.  The rows left stand
+  // at (4, 6), (2, 6) or (2, 4); row 1 is at 2, 4 or 6, and moves on from 2 with
+  // the exchange.
+  const bool later = fabs(F[2][1]) > fabs(F[1][1]);
+  const bool row1_at6 = at == 3 || (at == 1 && later);
+  double Lr[3];  // the even row left: columns 6 7, rhs
+  double Pv[4];  // pivot of column 2: columns 2 6 7, rhs
+#pragma unroll
+  for (int j = 0; j < 4; ++j) Pv[j] = later ? F[2][j + 1] : F[1][j + 1];
+  if (fabs(Pv[0]) < 1e-10) return false;
+  {
+    const double f = (later ? F[1][1] : F[2][1]) / Pv[0];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) Lr[j] = (later ? F[1][j + 2] : F[2][j + 2]) - f * Pv[j + 1];
+  }
+  // odd rows and the even row left, in the order of rows 3 .. 7; columns 3 .. 7, rhs
+  double O[5][6];
+#pragma unroll
+  for (int r = 0; r < 5; ++r) {
+    // rows 3 5 7 hold points 1 2 3; of rows 4 and 6 one holds point 0, the other the even row
+    const bool even = r == 1 ? row1_at6 : (r == 3 ? !row1_at6 : false);
+    const int i = r == 0 ? 1 : (r == 2 ? 2 : (r == 4 ? 3 : 0));
+    const double x = s1 * (sx[i] - c1x), y = s1 * (sy[i] - c1y), v = s2 * (dy[i] - c2y);
+    O[r][0] = even ? 0.0 : x;
+    O[r][1] = even ? 0.0 : y;
+    O[r][2] = even ? 0.0 : 1.0;
+    O[r][3] = even ? Lr[0] : -x * v;
+    O[r][4] = even ? Lr[1] : -y * v;
+    O[r][5] = even ? Lr[2] : v;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (!pivot_rows(O, k, k)) return false;
+    eliminate_rows(O, k, k);
+  }
+  if (fabs(O[4][4]) < 1e-10) return false;
+  double h[8];
+  h[7] = O[4][5] / O[4][4];
+  h[6] = (O[3][5] - O[3][4] * h[7]) / O[3][3];
+  h[5] = (O[2][5] - O[2][3] * h[6] - O[2][4] * h[7]) / O[2][2];
+  h[4] = (O[1][5] - O[1][2] * h[5] - O[1][3] * h[6] - O[1][4] * h[7]) / O[1][1];
+  h[3] = (O[0][5] - O[0][1] * h[4] - O[0][2] * h[5] - O[0][3] * h[6] - O[0][4] * h[7]) / O[0][0];
+  h[2] = (Pv[3] - Pv[1] * h[6] - Pv[2] * h[7]) / Pv[0];
+  h[1] = (F[0][4] - F[0][1] * h[2] - F[0][2] * h[6] - F[0][3] * h[7]) / F[0][0];
+  h[0] = (E[0][5] - E[0][1] * h[1] - E[0][2] * h[2] - E[0][3] * h[6] - E[0][4] * h[7]) / E[0][0];
   return denormalise(h, s1, c1x, c1y, s2, c2x, c2y, Hout);
 }
 
