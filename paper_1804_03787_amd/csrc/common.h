@@ -239,8 +239,14 @@ __host__ __device__ inline void cover_range(int n, int B, int nb, int c, int& lo
 
 // Half-sweeps of a whole pass (search.hip): what a launch is told.  SM_FIRST:
 // the pass's first half-sweep of the colour, which computes the pixels' current
-// costs and ignores what earlier half-sweeps noted; SM_LAST: its last one.
+// costs and ignores what earlier half-sweeps noted; SM_LAST: the last one of the
+// last pass, which leaves no notes behind.  Those of an earlier pass stay in win
+// until the next assignment, which takes them for what they are, unassigned: the
+// last half-sweep of the second colour still needs the first colour's (without
+// them it offers every neighbour again, at 1024x436 half as long again).
 enum { SM_RESTRICTED = 1, SM_FIRST = 2, SM_LAST = 4 };
+// The largest note (search.hip) as an int, below any assignment or filling.
+constexpr int32_t kLastNote = (int32_t)0x83ffffff;
 
 // Workgroups over which a half-sweep of one pair is spread before one takes more
 // pixels than a wave has lane groups.  A workgroup's pixels are sorted by work,

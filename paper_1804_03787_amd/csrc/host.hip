@@ -364,9 +364,10 @@ msgpm_status run_halfsweep(const Ctx& c, int colour, int it, int slot, int restr
   return two_lists(c, [&](int ident, hipStream_t s) { return launch_pm_restricted(c.P, c.w, colour, it, slot, ident, fresh, s); });
 }
 
-// SM_* bits of half-sweep `it` of a pass.
-int search_mode(int restricted, int it, int iters) {
-  return (restricted ? SM_RESTRICTED : 0) | (it == 0 ? SM_FIRST : 0) | (it == iters - 1 ? SM_LAST : 0);
+// SM_* bits of half-sweep `it` of the pass after level slot - 1 (0: the initial one).
+int search_mode(const DevParams& P, int slot, int it) {
+  return (slot ? SM_RESTRICTED : 0) | (it == 0 ? SM_FIRST : 0) |
+         (slot == P.n_levels && it == P.iters - 1 ? SM_LAST : 0);
 }
 
 // A pass of half-sweeps; a restricted pass reads the lists built before it.
@@ -383,7 +384,7 @@ msgpm_status run_pm_pass(const Ctx& c, int slot, int restricted) {
   msgpm_status st = check(timed(MSGPM_T_FEATURES, c.s, [&] { return launch_moments(c.P, c.w, c.s); }), "moments");
   for (int it = 0; it < c.P.iters && st == MSGPM_OK; ++it)
     for (int colour = 0; colour < 2 && st == MSGPM_OK; ++colour) {
-      const int mode = search_mode(restricted, it, c.P.iters);
+      const int mode = search_mode(c.P, slot, it);
       if (!restricted)
         st = check(timed(MSGPM_T_PM_INIT, c.s, [&] { return launch_search(c.P, c.w, colour, it, slot, mode, 1, c.s); }), "pm_halfsweep");
       else
@@ -742,7 +743,7 @@ std::vector<BatchStep> batch_schedule(const DevParams& P) {
   if (P.iters > 0) add(BK_MOMENTS, MSGPM_T_FEATURES);
   for (int it = 0; it < P.iters; ++it)
     for (int colour = 0; colour < 2; ++colour)
-      add(BK_PM_INIT, MSGPM_T_PM_INIT, colour, it, 0, search_mode(0, it, P.iters));
+      add(BK_PM_INIT, MSGPM_T_PM_INIT, colour, it, 0, search_mode(P, 0, it));
   for (int l = 0; l < P.n_levels; ++l) {
     for (int stage = 1; stage <= 2; ++stage) {
       add(BK_RANSAC, MSGPM_T_RANSAC, l, stage);
@@ -764,7 +765,7 @@ std::vector<BatchStep> batch_schedule(const DevParams& P) {
     if (P.iters > 0) add(BK_MOMENTS, MSGPM_T_FEATURES);
     for (int it = 0; it < P.iters; ++it)
       for (int colour = 0; colour < 2; ++colour) {
-        const int mode = search_mode(1, it, P.iters);
+        const int mode = search_mode(P, l + 1, it);
         add(BK_PM_RESTRICTED, MSGPM_T_PM_RESTRICTED, colour, it, l + 1, mode);
         add(BK_PM_RESTRICTED_IDENT, MSGPM_T_PM_RESTRICTED_IDENT, colour, it, l + 1, mode);
       }

@@ -1002,6 +1002,7 @@ __device__ __forceinline__ void assign_body(const DevParams& P, const Ws& w, Blk
   if (p >= W * Hh) return;
   const int x = p % W, y = p / W;
   int bwin = w.win[dir][p];
+  if (bwin <= kLastNote) bwin = -1;  // a note of the PatchMatch pass before
   double bl = w.loss[dir][p];
   // stage 2 offers only the residual pixels (Sec. 3.2); with the strict level
   // priority (Sec. 3.3) every stage does: an assigned pixel keeps its plane

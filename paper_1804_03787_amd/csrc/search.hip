@@ -46,6 +46,7 @@ namespace msgpm {
 // half-sweep changed its offset, and the tried positions around its best
 // ((dy + 2) * 5 + dx + 2).  -1, the value outside passes, reads as changed.
 constexpr unsigned kMemoSign = 0x80000000u, kMemoChanged = 1u << 25, kMemoTried = (1u << 25) - 1u;
+static_assert((int32_t)(kMemoSign | kMemoChanged | kMemoTried) == kLastNote, "notes end at kLastNote");
 
 constexpr int kTgtRows = 16;          // random-search radii: at most 15; neighbours and plane: 5
 constexpr unsigned kRefresh = 1u << 31;  // in a candidate mask: the current cost first
