@@ -448,8 +448,8 @@ def main() -> int:
                          "plus an eager pass with HIP events around every launch for the per-kernel figures)")
     ap.add_argument("--fp16", action="store_true", help="FP16 feature storage (FP32 accumulation)")
     ap.add_argument("--two-streams", action="store_true",
-                    help="restricted half-sweeps' two launches side by side on two streams (library default) "
-                         "instead of in sequence on one")
+                    help="restricted half-sweeps as the library runs them by default, as one launch, "
+                         "instead of as two in sequence")
     ap.add_argument("--seed", type=int, default=0, help="scene seed of the 1024x436 generator")
     ap.add_argument("--cues", action="store_true", help="occlusion cues 2 (uniqueness) and 3 (overlap) on")
     ap.add_argument("--fill", type=int, default=0, help="half-sweeps of filling by model propagation (0 = none)")
@@ -555,10 +555,10 @@ def main() -> int:
     launches = {k: v[1] / args.steps for k, v in timing.items()}
     r, C = params["r"], params["C"]
 
-    # each PatchMatch kernel on its own: by default the restricted half-sweeps'
-    # two launches run in sequence on one stream (MSGPM_FLAG_ONE_STREAM), so the
-    # timed eager steps give each kernel's own time; with --two-streams they
-    # run side by side there, and an equal number of one-stream steps is timed
+    # each PatchMatch kernel on its own: by default the restricted half-sweeps
+    # run as two launches in sequence (MSGPM_FLAG_ONE_STREAM), so the timed
+    # eager steps give each kernel's own time; with --two-streams they are one
+    # launch there, and an equal number of two-launch steps is timed
     alone_ms, alone_n = kernel_ms, launches
     if args.two_streams:
         g1 = msgpm.Pair(W, H, **dict(params, one_stream=True))

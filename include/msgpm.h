@@ -84,16 +84,16 @@ typedef enum msgpm_status {
    incumbent when its loss is strictly smaller, the level breaking exact ties
    in favour of the coarser one (key (L, level, stage, window)). */
 #define MSGPM_FLAG_MERGE_STRICT 16u
-/* Execution option, not part of the method: the two launches of each
-   restricted half-sweep (pixels with a region plane, pixels without) are
-   issued one after the other on the caller's stream instead of side by side
-   on the caller's stream and a second stream of the library's.  Results are
-   the same either way (the two launches update disjoint pixels and read only
-   the other colour); with the flag the library creates no second stream, and
-   the per-kind kernel times of msgpm_timing_read are each kernel's own,
-   without the other's interference.  msgpm_solve_static always runs this
-   way.  Ignored by the batched and served forms, which take every pair's
-   restricted half-sweep in shared launches of their own. */
+/* Execution option, not part of the method: each restricted half-sweep of the
+   single-pair forms runs as two launches, first the pixels with a region plane,
+   then those without, instead of as one (msgpm_solve) or as two side by side on
+   the caller's stream and a second stream of the library's (msgpm_pm_halfsweep).
+   Results are the same either way (the two sets of pixels are disjoint and read
+   only the other colour); with the flag the per-kind kernel times of
+   msgpm_timing_read are each kernel's own, without the other's interference, and
+   the library creates no second stream.  While kernel timing is enabled, the
+   single-pair forms run as two launches without the flag too.  Ignored by
+   msgpm_solve_static and the batched and served forms. */
 #define MSGPM_FLAG_ONE_STREAM 32u
 
 /* Method parameters.  Defaults in brackets are those of the 1024x436 workload. */
@@ -197,9 +197,7 @@ const char* msgpm_last_error(void);
  *                   (no plane of its own: occluded by the same rule, with a
  *                   neighbour's plane flow).
  * The plane table stays in the workspace (layout.planes).  Work is enqueued
- * on `stream` and the call returns; the identity-patch half of each restricted
- * half-sweep runs on a second stream of the calling thread (created on first
- * use, default priority), forked from and joined back into `stream` by events.
+ * on `stream` and the call returns.
  * ------------------------------------------------------------------------- */
 msgpm_status msgpm_solve(const msgpm_params* p, const float* d_rgb1, const float* d_rgb2,
                          const int32_t* d_init_nnf0, const int32_t* d_init_nnf1, void* d_ws,
@@ -322,10 +320,9 @@ msgpm_status msgpm_graph_cache_clear(void);
  * total_bytes exceeds it are rejected with MSGPM_E_INVALID and nothing is
  * enqueued.  Frames, initial NNF and outputs are as for msgpm_solve; d_planes
  * (may be NULL) receives the plane table, layout.n_planes records, by a
- * device-to-device copy.  Everything runs on `stream`, in order (the two
- * launches of a restricted half-sweep one after the other, with the results
- * of msgpm_solve bit for bit); no stream, event, graph or memory is created
- * and kernel timing does not see these launches.  All calls on one GPU share
+ * device-to-device copy.  Everything runs on `stream`, in order,
+ * with the results of msgpm_solve bit for bit; no stream, event, graph or memory
+ * is created and kernel timing does not see these launches.  All calls on one GPU share
  * its array, and the array keeps the last call's state: calls that overlap on
  * one GPU (two streams, two threads) race and corrupt each other, so callers
  * must order them. */
@@ -492,7 +489,8 @@ enum {
   MSGPM_T_INIT = 1,
   MSGPM_T_EVAL_COST = 2,
   MSGPM_T_PM_INIT = 3,       /* PatchMatch half-sweeps of the initial pass (identity patches) */
-  MSGPM_T_PM_RESTRICTED = 4, /* restricted half-sweeps, pixels with a region plane (distorted patches) */
+  MSGPM_T_PM_RESTRICTED = 4, /* restricted half-sweeps, pixels with a region plane (distorted patches);
+                                batched forms: whole restricted half-sweeps */
   MSGPM_T_RANSAC = 5,
   MSGPM_T_ASSIGN = 6,
   MSGPM_T_SYMMETRY = 7,

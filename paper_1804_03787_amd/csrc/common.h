@@ -284,10 +284,12 @@ hipError_t launch_pm_restricted(const DevParams& P, const Ws& w, int colour, int
                                 int fresh, hipStream_t s);
 // whole passes: the patch moments of both frames (over the tentative assignment,
 // which a pass does not use), then half-sweeps with SM_* bits; a restricted one
-// over one of the two lists
+// over one of the two lists or (launch_search_lists) both
 hipError_t launch_moments(const DevParams& P, const Ws& w, hipStream_t s);
 hipError_t launch_search(const DevParams& P, const Ws& w, int colour, int iter, int slot, int mode, int ident,
                          hipStream_t s);
+hipError_t launch_search_lists(const DevParams& P, const Ws& w, int colour, int iter, int slot, int mode,
+                               hipStream_t s);
 hipError_t launch_ransac(const DevParams& P, const Ws& w, int level, int stage, hipStream_t s);
 hipError_t launch_assign(const DevParams& P, const Ws& w, int level, int stage, int tentative, hipStream_t s);
 hipError_t launch_symmetry(const DevParams& P, const Ws& w, int level, int stage, hipStream_t s);
@@ -313,8 +315,7 @@ enum BatchKind {
   BK_ACTIVE_LIST,   // a = {colour}
   BK_MOMENTS,       // grid.y = frame
   BK_PM_INIT,       // a = {colour, iter, slot, SM_* bits}
-  BK_PM_RESTRICTED, // the same, pixels with a region plane
-  BK_PM_RESTRICTED_IDENT,  // the same, pixels without one
+  BK_PM_RESTRICTED, // the same over both lists
   BK_RANSAC,        // a = {level, stage}
   BK_ASSIGN,        // a = {level, stage, tentative}
   BK_SYMMETRY,      // a = {level, stage}

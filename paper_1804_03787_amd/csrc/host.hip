@@ -115,10 +115,13 @@ struct Range {
   }
 };
 
+// Whether launches are being timed, each by events of its own.
+bool timing() { return g_timer.on && !g_capturing && !g_no_events; }
+
 template <class F>
 hipError_t timed(int kind, hipStream_t s, F&& launch) {
   Range range(kPhaseNames[kind]);
-  if (!g_timer.on || g_capturing || g_no_events) return launch();
+  if (!timing()) return launch();
   std::lock_guard<std::mutex> lk(g_timer.mu);
   hipEvent_t a = g_timer.get(), b = g_timer.get();
   if (!a || !b) return hipErrorOutOfMemory;
@@ -272,7 +275,7 @@ struct Ctx {
   msgpm_layout L;
   Ws w;
   hipStream_t s;
-  bool one_stream = false;  // restricted half-sweeps: both launches on s, one after the other
+  bool one_stream = false;  // restricted half-sweeps as two launches on s, one after the other
 };
 
 msgpm_status open_ctx(const msgpm_params* p, void* ws, void* stream, Ctx* c) {
@@ -293,7 +296,7 @@ msgpm_status check_level(const Ctx& c, int level, int stage) {
 }
 
 // A second stream of the calling thread (one per device), on which the
-// identity-patch launch of a restricted half-sweep runs beside the
+// identity-patch launch of a single restricted half-sweep runs beside its
 // distorted-patch launch: the two update disjoint pixels of one colour and
 // only read the other colour.  Created on first use and kept for the life of
 // the thread; default priority.
@@ -337,11 +340,11 @@ msgpm_status run_lists(const Ctx& c) {
   return check(timed(MSGPM_T_PM_LIST, c.s, [&] { return launch_pm_lists(c.P, c.w, c.s); }), "pm_list");
 }
 
-// The two launches of a restricted half-sweep, launch(ident, stream): pixels with
-// a region plane (ident = 0) and without.  They update disjoint pixels and read
+// A restricted half-sweep as two launches, launch(ident, stream): pixels with a
+// region plane (ident = 0) and without.  They update disjoint pixels and read
 // only the other colour, so that one after the other they give the same
 // result as side by side (distorted patches on the caller's stream, identity
-// patches on the second one).
+// patches on the second one), and as in one launch.
 template <class F>
 msgpm_status two_lists(const Ctx& c, F&& launch) {
   auto run = [&](int ident, hipStream_t s) {
@@ -387,6 +390,8 @@ msgpm_status run_pm_pass(const Ctx& c, int slot, int restricted) {
       const int mode = search_mode(c.P, slot, it);
       if (!restricted)
         st = check(timed(MSGPM_T_PM_INIT, c.s, [&] { return launch_search(c.P, c.w, colour, it, slot, mode, 1, c.s); }), "pm_halfsweep");
+      else if (!c.one_stream && !timing())  // one launch has no time of either kind
+        st = check(timed(MSGPM_T_PM_RESTRICTED, c.s, [&] { return launch_search_lists(c.P, c.w, colour, it, slot, mode, c.s); }), "pm_restricted");
       else
         st = two_lists(c, [&](int ident, hipStream_t s) { return launch_search(c.P, c.w, colour, it, slot, mode, ident, s); });
     }
@@ -628,8 +633,6 @@ msgpm_status msgpm_solve_graph(const msgpm_params* p, const float* d_rgb1, const
   const void* ptrs[] = {d_rgb1, d_rgb2, d_init_nnf0, d_init_nnf1, d_ws, d_flow0, d_flow1, d_occ0, d_occ1};
   std::string key(reinterpret_cast<const char*>(p), sizeof *p);
   key.append(reinterpret_cast<const char*>(ptrs), sizeof ptrs);
-  Aux* aux = nullptr;  // created outside the capture; joins it through the fork event
-  if (!c.one_stream && (st = check(aux_stream(&aux), "second stream")) != MSGPM_OK) return st;
   return cached_graph_launch(key, c.s, [&](hipStream_t cs) {
     Ctx cc = c;
     cc.s = cs;
@@ -701,8 +704,7 @@ extern "C" msgpm_status msgpm_solve_static(const msgpm_params* p, const float* d
   if ((st = scratch_address(&base)) != MSGPM_OK) return st;
   c.w = make_ws(c.P, c.L, base);
   c.s = static_cast<hipStream_t>(stream);
-  c.one_stream = true;  // no second stream: nothing is created
-  NoEvents quiet;       // no timing events either
+  NoEvents quiet;  // no timing events are created
   // every array the pipeline reads is written by it first (features with their
   // pad pixel, initial state, plane records, counters, lists), so what earlier
   // calls left in the array does not matter
@@ -767,7 +769,6 @@ std::vector<BatchStep> batch_schedule(const DevParams& P) {
       for (int colour = 0; colour < 2; ++colour) {
         const int mode = search_mode(P, l + 1, it);
         add(BK_PM_RESTRICTED, MSGPM_T_PM_RESTRICTED, colour, it, l + 1, mode);
-        add(BK_PM_RESTRICTED_IDENT, MSGPM_T_PM_RESTRICTED_IDENT, colour, it, l + 1, mode);
       }
   }
   if (P.fill_sweeps > 0) {
@@ -835,7 +836,6 @@ msgpm_tuning tune_for(int r, int C, int fp16) {
 int tune_class(int kind) {
   switch (kind) {
     case BK_PM_INIT:
-    case BK_PM_RESTRICTED_IDENT:
     case BK_EVAL_COST_IDENT:
       return MSGPM_TUNE_PM_IDENTITY;
     case BK_PM_RESTRICTED:
@@ -1156,10 +1156,18 @@ msgpm_status msgpm_timing_read(double* ms, int64_t* launches) {
 namespace {
 
 constexpr int kCohorts = MSGPM_SERVER_MAX_COHORTS;  // cohorts in flight at most (and server streams)
-// Launches of one pipeline a region holds: the 4096 of the limit, beside which
-// the launches that compute moments, one per PatchMatch pass, do not count.
+// Limit on the launches of a served pipeline, counted as one per phase step
+// (served_launches), and those a region has room for: a batch makes fewer of
+// them for restricted half-sweeps, and one more per PatchMatch pass (moments).
 constexpr int kMaxLaunches = 4096;
 constexpr int kMaxMoments = 1 + MSGPM_MAX_LEVELS;
+
+size_t served_launches(const DevParams& P) {
+  const size_t it = P.iters;
+  const size_t level = 8 + 2 + (P.cues & MSGPM_FLAG_CUE_UNIQUE ? 4 : 0) + 1 + 3 + (it ? 4 * it : 2);
+  return (P.histeq ? 3 : 0) + 1 + 2 + (it ? 2 * it : 1) + P.n_levels * level +
+         (P.fill_sweeps > 0 ? 1 + (size_t)P.fill_sweeps : 0) + 2;
+}
 constexpr int kMaxLists = 48;        // distinct item lists of one pipeline
 
 struct Slot {
@@ -1296,8 +1304,7 @@ msgpm_status msgpm_server_submit(msgpm_server* sv, const msgpm_params* p, const 
     delete q;
     return fail(MSGPM_E_INVALID, "NULL or misaligned buffer");
   }
-  size_t steps = 0;
-  for (const BatchStep& b : batch_schedule(q->P)) steps += b.kind != BK_MOMENTS;
+  const size_t steps = served_launches(q->P);
   if (steps > (size_t)kMaxLaunches) {
     delete q;
     return fail(MSGPM_E_UNSUPPORTED, "a served pipeline has at most %d launches (these parameters give %zu)",

@@ -432,15 +432,15 @@ __device__ inline int group_geometry(bool ok, bool integral, int base) {
 // Adds the lane's taps of rows [T0, T1) for target (tx, ty) to acc, in row
 // order.  Integral geometry: one pixel per tap.  Otherwise bilinear: the
 // corner pairs of the tap's two rows, each one contiguous load.  Rows are
-// taken three at a time: all their loads are issued first and a scheduling
+// taken CH at a time: all their loads are issued first and a scheduling
 // barrier keeps them ahead of the arithmetic, so a wave has the gathers of
-// three rows in flight instead of waiting on each row in turn.
-template <int R, int C, bool FP16, bool IDENT, bool INTEGRAL, int T0, int T1>
+// CH rows in flight instead of waiting on each row in turn.
+template <int R, int C, bool FP16, bool IDENT, bool INTEGRAL, int T0, int T1, int CH = 3>
 __device__ inline float add_rows(float acc, const LaneCol<R, C, IDENT>& L, Feat F2, int W, int H,
                                  int tx, int ty, float gw) {
-  if constexpr (T1 - T0 > 3) {
-    acc = add_rows<R, C, FP16, IDENT, INTEGRAL, T0, T0 + 3>(acc, L, F2, W, H, tx, ty, gw);
-    return add_rows<R, C, FP16, IDENT, INTEGRAL, T0 + 3, T1>(acc, L, F2, W, H, tx, ty, gw);
+  if constexpr (T1 - T0 > CH) {
+    acc = add_rows<R, C, FP16, IDENT, INTEGRAL, T0, T0 + CH, CH>(acc, L, F2, W, H, tx, ty, gw);
+    return add_rows<R, C, FP16, IDENT, INTEGRAL, T0 + CH, T1, CH>(acc, L, F2, W, H, tx, ty, gw);
   } else if constexpr (IDENT || INTEGRAL) {
     constexpr int N = T1 - T0;
     uint32_t v[N][Px<C, FP16>::kWords];
@@ -518,23 +518,23 @@ __device__ inline float add_rows(float acc, const LaneCol<R, C, IDENT>& L, Feat 
 // never be strictly better, is dropped (rejected = true).  An accepted
 // candidate is summed in the same order as without the checks.  rows returns
 // the tap rows computed.
-template <int R, int C, bool FP16, bool IDENT, bool INTEGRAL, bool EE>
+template <int R, int C, bool FP16, bool IDENT, bool INTEGRAL, bool EE, int CH = 3>
 __device__ inline float group_cost(const LaneCol<R, C, IDENT>& L, Feat F2, int W, int H, int tx,
                                    int ty, float gw, int base, float bound, bool& rejected, unsigned& rows) {
   constexpr int T = 2 * R + 1, T1 = T / 3, T2 = (2 * T) / 3;
   rejected = false;
   if constexpr (!EE) {
     rows += T;
-    return group_sum<T>(add_rows<R, C, FP16, IDENT, INTEGRAL, 0, T>(0.f, L, F2, W, H, tx, ty, gw), base);
+    return group_sum<T>(add_rows<R, C, FP16, IDENT, INTEGRAL, 0, T, CH>(0.f, L, F2, W, H, tx, ty, gw), base);
   } else {
-    float acc = add_rows<R, C, FP16, IDENT, INTEGRAL, 0, T1>(0.f, L, F2, W, H, tx, ty, gw);
+    float acc = add_rows<R, C, FP16, IDENT, INTEGRAL, 0, T1, CH>(0.f, L, F2, W, H, tx, ty, gw);
     rows += T1;
     rejected = true;
     if (group_sum<T>(acc, base) >= bound) return 0.f;
-    acc = add_rows<R, C, FP16, IDENT, INTEGRAL, T1, T2>(acc, L, F2, W, H, tx, ty, gw);
+    acc = add_rows<R, C, FP16, IDENT, INTEGRAL, T1, T2, CH>(acc, L, F2, W, H, tx, ty, gw);
     rows += T2 - T1;
     if (group_sum<T>(acc, base) >= bound) return 0.f;
-    acc = add_rows<R, C, FP16, IDENT, INTEGRAL, T2, T>(acc, L, F2, W, H, tx, ty, gw);
+    acc = add_rows<R, C, FP16, IDENT, INTEGRAL, T2, T, CH>(acc, L, F2, W, H, tx, ty, gw);
     rows += T - T2;
     rejected = false;
     return group_sum<T>(acc, base);

@@ -1552,7 +1552,6 @@ int batch_blocks(int kind, const DevParams& P, const int* a) {
     case BK_MOMENTS:
     case BK_PM_INIT:
     case BK_PM_RESTRICTED:
-    case BK_PM_RESTRICTED_IDENT:
       return pm_batch_blocks(kind, P, a);
     default:
       return px;
@@ -1577,7 +1576,6 @@ hipError_t launch_batched(int kind, const DevParams& P0, const uint8_t* tab, int
     case BK_MOMENTS:
     case BK_PM_INIT:
     case BK_PM_RESTRICTED:
-    case BK_PM_RESTRICTED_IDENT:
       return launch_batched_search(kind, P0, tab, k, grid, A, persist, s);
     default:
       return launch_batched_planes(kind, tab, k, grid, lds, A, s);

@@ -373,6 +373,8 @@ __device__ inline int sort_by_work(SearchLds& S, int phase, int most) {
 template <int R, int C, bool FP16, bool IDENT>
 __device__ inline void evaluate(const DevParams& P, const Ws& w, int dir, SearchLds& S, int phase, unsigned& rows_out) {
   constexpr int G = 2 * R + 1, NG = kWave / G;
+  // rows of a distorted patch in flight: two of FP16 records fit 4 waves per SIMD
+  constexpr int kChunk = FP16 ? 2 : 3;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane / G, j = lane - g * G, base = g * G;
   const int W = P.W, H = P.H;
@@ -410,9 +412,9 @@ __device__ inline void evaluate(const DevParams& P, const Ws& w, int dir, Search
       if (geo == 2)
         bc = __builtin_huge_valf();
       else if (IDENT || geo == 1)
-        bc = group_cost<R, C, FP16, IDENT, true, false>(L, F2, W, H, xy_x(best), xy_y(best), gw, base, 0.f, rejected, r0);
+        bc = group_cost<R, C, FP16, IDENT, true, false, kChunk>(L, F2, W, H, xy_x(best), xy_y(best), gw, base, 0.f, rejected, r0);
       else
-        bc = group_cost<R, C, FP16, IDENT, IDENT, false>(L, F2, W, H, xy_x(best), xy_y(best), gw, base, 0.f, rejected, r0);
+        bc = group_cost<R, C, FP16, IDENT, IDENT, false, kChunk>(L, F2, W, H, xy_x(best), xy_y(best), gw, base, 0.f, rejected, r0);
     }
     m &= geo == 2 ? 0u : ~kRefresh;
     // the candidate of the lowest bound, then the others in order.  A cost equal
@@ -441,9 +443,9 @@ __device__ inline void evaluate(const DevParams& P, const Ws& w, int dir, Search
         if (won) {
           bool rejected;
           if (geo == 1)
-            c = group_cost<R, C, FP16, IDENT, true, true>(L, F2, W, H, xy_x(t), xy_y(t), gw, base, top, rejected, rows);
+            c = group_cost<R, C, FP16, IDENT, true, true, kChunk>(L, F2, W, H, xy_x(t), xy_y(t), gw, base, top, rejected, rows);
           else
-            c = group_cost<R, C, FP16, IDENT, IDENT, true>(L, F2, W, H, xy_x(t), xy_y(t), gw, base, top, rejected, rows);
+            c = group_cost<R, C, FP16, IDENT, IDENT, true, kChunk>(L, F2, W, H, xy_x(t), xy_y(t), gw, base, top, rejected, rows);
           won = !rejected && c < top;
         }
       }
@@ -616,10 +618,9 @@ __host__ __device__ inline int tile_rows(int W, int H, int nx) {
 // launch has a workgroup per tile, otherwise in runs.  Restricted: the listed
 // pixels.
 template <int R, int C, bool FP16, bool IDENT>
-__device__ __forceinline__ void search_body(const DevParams& P, const Ws& w, Blk bk, int colour, int iter, int slot,
-                                            int mode) {
+__device__ __forceinline__ void search_body(const DevParams& P, const Ws& w, SearchLds& S, Blk bk, int colour, int iter,
+                                            int slot, int mode) {
   constexpr int G = 2 * R + 1, NG = kWave / G;
-  __shared__ SearchLds S;
   const int t = threadIdx.x;
   const int dir = bk.y;
   const int W = P.W, H = P.H;
@@ -685,24 +686,68 @@ __device__ __forceinline__ void search_body(const DevParams& P, const Ws& w, Blk
 // Waves per SIMD the registers are held to.  Measured on MI355X at 1024x436, per
 // pair: identity patches of FP16 records at 5 waves 6.8 ms, at 4 7.4 ms; of FP32
 // records at 5 (with spills) 16.4 ms, at 4 10.3 ms.
-constexpr int search_waves(bool fp16, bool ident) { return ident ? (fp16 ? 5 : 4) : 3; }
+// Both lists in one launch: FP16 records at 4 waves (distorted patches with two
+// rows in flight) 14.6 ms, at 3 (with three) 15.1.
+constexpr int search_waves(bool fp16, bool ident) { return ident ? (fp16 ? 5 : 4) : (fp16 ? 4 : 3); }
 
 template <int R, int C, bool FP16, bool IDENT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(search_waves(FP16, IDENT)))) void k_search(
     DevParams P, Ws w, int colour, int iter, int slot, int mode) {
-  search_body<R, C, FP16, IDENT>(P, w, blk_here(), colour, iter, slot, mode);
+  __shared__ SearchLds S;
+  search_body<R, C, FP16, IDENT>(P, w, S, blk_here(), colour, iter, slot, mode);
 }
 
-template <int R, int C, bool FP16, bool IDENT, bool LOOP>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(search_waves(FP16, IDENT)))) void kb_search(
+// Both lists of a restricted half-sweep: the first half of a direction's workgroups
+// (a multiple of kXcds) takes the pixels with a region plane, the second half
+// the others, which then fill the tail that the first leave.  Two launches on
+// two streams cost 12 us a half-sweep for their fork and join alone: 320x240
+// FP32 5.48 -> 5.10 ms per pair, 1024x436 20.55 -> 19.5 (FP16 15.6 -> 15.1),
+// 2048x872 81.1 -> 80.4 (71.9 -> 71.6).
+template <int R, int C, bool FP16>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(search_waves(FP16, false)))) void k_search_lists(
+    DevParams P, Ws w, int colour, int iter, int slot, int mode) {
+  __shared__ SearchLds S;
+  Blk bk = blk_here();
+  bk.nx >>= 1;
+  if (bk.x < bk.nx) {
+    search_body<R, C, FP16, false>(P, w, S, bk, colour, iter, slot, mode);
+  } else {
+    bk.x -= bk.nx;
+    search_body<R, C, FP16, true>(P, w, S, bk, colour, iter, slot, mode);
+  }
+}
+
+template <int R, int C, bool FP16, bool LOOP>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(search_waves(FP16, true)))) void kb_search(
     const uint8_t* __restrict__ tab, int k, BArgs A) {
   const BatchView V = batch_view(tab, k);
   const PairDesc* __restrict__ pd = V.pd;
   const Item* __restrict__ it = V.it;
   const int n = V.n, total = V.total;
+  __shared__ SearchLds S;
   for_each_item<true, LOOP>(it, n, total, [&](int i, Blk bk) {
     const Item& I = it[i];
-    search_body<R, C, FP16, IDENT>(pd[I.pair].P, pd[I.pair].w, bk, A.a[0], A.a[1], A.a[2], A.a[3]);
+    search_body<R, C, FP16, true>(pd[I.pair].P, pd[I.pair].w, S, bk, A.a[0], A.a[1], A.a[2], A.a[3]);
+  });
+}
+
+template <int R, int C, bool FP16, bool LOOP>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(search_waves(FP16, false)))) void
+kb_search_lists(const uint8_t* __restrict__ tab, int k, BArgs A) {
+  const BatchView V = batch_view(tab, k);
+  const PairDesc* __restrict__ pd = V.pd;
+  const Item* __restrict__ it = V.it;
+  const int n = V.n, total = V.total;
+  __shared__ SearchLds S;
+  for_each_item<true, LOOP>(it, n, total, [&](int i, Blk bk) {
+    const Item& I = it[i];
+    bk.nx >>= 1;
+    if (bk.x < bk.nx) {
+      search_body<R, C, FP16, false>(pd[I.pair].P, pd[I.pair].w, S, bk, A.a[0], A.a[1], A.a[2], A.a[3]);
+    } else {
+      bk.x -= bk.nx;
+      search_body<R, C, FP16, true>(pd[I.pair].P, pd[I.pair].w, S, bk, A.a[0], A.a[1], A.a[2], A.a[3]);
+    }
   });
 }
 
@@ -722,6 +767,9 @@ static int search_blocks(const DevParams& P) {
   return (n + run - 1) / run;
 }
 
+// The same for both lists in one launch: twice that, each half a multiple of kXcds.
+static int lists_blocks(const DevParams& P) { return 2 * ((search_blocks(P) + kXcds - 1) / kXcds * kXcds); }
+
 template <int R, int C, bool FP16>
 static hipError_t dispatch_search(const DevParams& P, const Ws& w, int colour, int iter, int slot, int mode, int ident,
                                   hipStream_t s) {
@@ -733,27 +781,40 @@ static hipError_t dispatch_search(const DevParams& P, const Ws& w, int colour, i
   return hipGetLastError();
 }
 
+template <int R, int C, bool FP16>
+static hipError_t dispatch_search_lists(const DevParams& P, const Ws& w, int colour, int iter, int slot, int mode,
+                                        hipStream_t s) {
+  hipLaunchKernelGGL((k_search_lists<R, C, FP16>), dim3(lists_blocks(P), 2), dim3(kBlock), 0, s, P, w, colour, iter,
+                     slot, mode);
+  return hipGetLastError();
+}
+
 template <int R, int C, bool FP16, bool LOOP>
-static void dispatch_search_form(bool ident, const uint8_t* tab, int k, dim3 grid, BArgs A, hipStream_t s) {
-  if (ident)
-    hipLaunchKernelGGL((kb_search<R, C, FP16, true, LOOP>), grid, dim3(kBlock), 0, s, tab, k, A);
+static void dispatch_search_form(bool initial, const uint8_t* tab, int k, dim3 grid, BArgs A, hipStream_t s) {
+  if (initial)
+    hipLaunchKernelGGL((kb_search<R, C, FP16, LOOP>), grid, dim3(kBlock), 0, s, tab, k, A);
   else
-    hipLaunchKernelGGL((kb_search<R, C, FP16, false, LOOP>), grid, dim3(kBlock), 0, s, tab, k, A);
+    hipLaunchKernelGGL((kb_search_lists<R, C, FP16, LOOP>), grid, dim3(kBlock), 0, s, tab, k, A);
 }
 
 template <int R, int C, bool FP16>
-static hipError_t dispatch_search_batched(bool ident, const uint8_t* tab, int k, int grid, BArgs A, bool persist,
+static hipError_t dispatch_search_batched(bool initial, const uint8_t* tab, int k, int grid, BArgs A, bool persist,
                                           hipStream_t s) {
   if (persist)
-    dispatch_search_form<R, C, FP16, true>(ident, tab, k, dim3(grid, 2), A, s);
+    dispatch_search_form<R, C, FP16, true>(initial, tab, k, dim3(grid, 2), A, s);
   else
-    dispatch_search_form<R, C, FP16, false>(ident, tab, k, dim3(grid, 2), A, s);
+    dispatch_search_form<R, C, FP16, false>(initial, tab, k, dim3(grid, 2), A, s);
   return hipGetLastError();
 }
 
 hipError_t launch_search(const DevParams& P, const Ws& w, int colour, int iter, int slot, int mode, int ident,
                          hipStream_t s) {
   MSGPM_DISPATCH(dispatch_search, P, w, colour, iter, slot, mode, ident, s);
+}
+
+hipError_t launch_search_lists(const DevParams& P, const Ws& w, int colour, int iter, int slot, int mode,
+                               hipStream_t s) {
+  MSGPM_DISPATCH(dispatch_search_lists, P, w, colour, iter, slot, mode, s);
 }
 
 hipError_t launch_moments(const DevParams& P, const Ws& w, hipStream_t s) {
@@ -782,11 +843,12 @@ hipError_t launch_batched_search(int kind, const DevParams& P0, const uint8_t* t
     }
     return hipGetLastError();
   }
-  MSGPM_DISPATCH(dispatch_search_batched, kind != BK_PM_RESTRICTED, tab, k, grid, A, persist, s);
+  MSGPM_DISPATCH(dispatch_search_batched, kind == BK_PM_INIT, tab, k, grid, A, persist, s);
 }
 
 int search_batch_blocks(int kind, const DevParams& P) {
-  return kind == BK_MOMENTS ? moments_blocks(P) : search_blocks(P);
+  if (kind == BK_MOMENTS) return moments_blocks(P);
+  return kind == BK_PM_INIT ? search_blocks(P) : lists_blocks(P);
 }
 
 }  // namespace msgpm
