@@ -291,7 +291,7 @@ hipError_t launch_search(const DevParams& P, const Ws& w, int colour, int iter, 
 hipError_t launch_search_lists(const DevParams& P, const Ws& w, int colour, int iter, int slot, int mode,
                                hipStream_t s);
 hipError_t launch_ransac(const DevParams& P, const Ws& w, int level, int stage, hipStream_t s);
-hipError_t launch_assign(const DevParams& P, const Ws& w, int level, int stage, int tentative, hipStream_t s);
+hipError_t launch_assign(const DevParams& P, const Ws& w, int level, int stage, int mode, hipStream_t s);
 hipError_t launch_symmetry(const DevParams& P, const Ws& w, int level, int stage, hipStream_t s);
 hipError_t launch_fb_unassign(const DevParams& P, const Ws& w, hipStream_t s);
 hipError_t launch_nnf_update(const DevParams& P, const Ws& w, int level, hipStream_t s);
@@ -317,7 +317,7 @@ enum BatchKind {
   BK_PM_INIT,       // a = {colour, iter, slot, SM_* bits}
   BK_PM_RESTRICTED, // the same over both lists
   BK_RANSAC,        // a = {level, stage}
-  BK_ASSIGN,        // a = {level, stage, tentative}
+  BK_ASSIGN,        // a = {level, stage, mode}
   BK_SYMMETRY,      // a = {level, stage}
   BK_FB,
   BK_COMMIT,

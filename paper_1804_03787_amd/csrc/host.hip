@@ -542,7 +542,7 @@ msgpm_status solve_sequence(const Ctx& c, const float* d_rgb1, const float* d_rg
       RUN(timed(MSGPM_T_RANSAC, c.s, [&] { return launch_ransac(c.P, c.w, l, stage, c.s); }), "ransac");
       RUN(timed(MSGPM_T_ASSIGN, c.s, [&] { return launch_assign(c.P, c.w, l, stage, 1, c.s); }), "assign");
       RUN(timed(MSGPM_T_SYMMETRY, c.s, [&] { return launch_symmetry(c.P, c.w, l, stage, c.s); }), "symmetry");
-      RUN(timed(MSGPM_T_ASSIGN, c.s, [&] { return launch_assign(c.P, c.w, l, stage, 0, c.s); }), "assign");
+      RUN(timed(MSGPM_T_ASSIGN, c.s, [&] { return launch_assign(c.P, c.w, l, stage, 2, c.s); }), "assign");
     }
     RUN(timed(MSGPM_T_FB, c.s, [&] { return launch_fb_unassign(c.P, c.w, c.s); }), "fb_unassign");
     if (c.P.cues & MSGPM_FLAG_CUE_UNIQUE) RUN(timed(MSGPM_T_FB, c.s, [&] { return launch_unique(c.P, c.w, c.s); }), "unique");
@@ -751,7 +751,7 @@ std::vector<BatchStep> batch_schedule(const DevParams& P) {
       add(BK_RANSAC, MSGPM_T_RANSAC, l, stage);
       add(BK_ASSIGN, MSGPM_T_ASSIGN, l, stage, 1);
       add(BK_SYMMETRY, MSGPM_T_SYMMETRY, l, stage);
-      add(BK_ASSIGN, MSGPM_T_ASSIGN, l, stage, 0);
+      add(BK_ASSIGN, MSGPM_T_ASSIGN, l, stage, 2);
     }
     add(BK_FB, MSGPM_T_FB);
     add(BK_COMMIT, MSGPM_T_FB);
