@@ -269,7 +269,7 @@ __host__ __device__ inline int search_run(unsigned cnt, int nx, int groups) {
 // ---- launch wrappers (defined in the .hip files) ---------------------------
 hipError_t launch_histeq(const DevParams& P, const Ws& w, const float* rgb1, const float* rgb2, hipStream_t s);
 int heq_hist_blocks(const DevParams& P);
-hipError_t launch_features(const DevParams& P, const Ws& w, const float* rgb, int frame, hipStream_t s);
+hipError_t launch_features(const DevParams& P, const Ws& w, const float* rgb1, const float* rgb2, hipStream_t s);
 hipError_t launch_init_state(const DevParams& P, const Ws& w, const int32_t* init0, const int32_t* init1,
                              hipStream_t s);
 hipError_t launch_eval_cost(const DevParams& P, const Ws& w, int mode, hipStream_t s);
@@ -279,7 +279,7 @@ hipError_t launch_pm_halfsweep(const DevParams& P, const Ws& w, int colour, int 
                                hipStream_t s);
 // restricted pass: the pixel lists, then one kernel per list; fresh: the
 // listed pixels' current costs are computed in the sweep (the mode-1 refresh)
-hipError_t launch_pm_lists(const DevParams& P, const Ws& w, hipStream_t s);
+hipError_t launch_pm_lists(const DevParams& P, const Ws& w, bool cleared, hipStream_t s);
 hipError_t launch_pm_restricted(const DevParams& P, const Ws& w, int colour, int iter, int slot, int ident,
                                 int fresh, hipStream_t s);
 // whole passes: the patch moments of both frames (over the tentative assignment,
@@ -293,8 +293,8 @@ hipError_t launch_search_lists(const DevParams& P, const Ws& w, int colour, int 
 hipError_t launch_ransac(const DevParams& P, const Ws& w, int level, int stage, hipStream_t s);
 hipError_t launch_assign(const DevParams& P, const Ws& w, int level, int stage, int mode, hipStream_t s);
 hipError_t launch_symmetry(const DevParams& P, const Ws& w, int level, int stage, hipStream_t s);
-hipError_t launch_fb_unassign(const DevParams& P, const Ws& w, hipStream_t s);
-hipError_t launch_nnf_update(const DevParams& P, const Ws& w, int level, hipStream_t s);
+hipError_t launch_fb_unassign(const DevParams& P, const Ws& w, bool commit, hipStream_t s);
+hipError_t launch_nnf_update(const DevParams& P, const Ws& w, int level, int commit, hipStream_t s);
 hipError_t launch_unique(const DevParams& P, const Ws& w, hipStream_t s);
 hipError_t launch_fill(const DevParams& P, const Ws& w, hipStream_t s);
 hipError_t launch_finalize(const DevParams& P, const Ws& w, float* flow0, float* flow1, uint8_t* occ0,
@@ -311,8 +311,7 @@ enum BatchKind {
   BK_INIT_PLANES,   // grid.y = 1
   BK_EVAL_COST_IDENT,  // a = {0}: identity-patch cost refresh
   BK_EVAL_COST_PLANE,  // a = {mode 1 or 2}: region-plane cost refresh
-  BK_ZERO_ACTIVE,   // one workgroup per item, grid.y = 1
-  BK_ACTIVE_LIST,   // a = {colour}
+  BK_ACTIVE_LIST,
   BK_MOMENTS,       // grid.y = frame
   BK_PM_INIT,       // a = {colour, iter, slot, SM_* bits}
   BK_PM_RESTRICTED, // the same over both lists
@@ -321,7 +320,7 @@ enum BatchKind {
   BK_SYMMETRY,      // a = {level, stage}
   BK_FB,
   BK_COMMIT,
-  BK_NNF_UPDATE,    // a = {level}
+  BK_NNF_UPDATE,    // a = {level, commit}
   BK_FINALIZE,
   BK_UNIQUE,        // a = {phase 0..3}: occlusion cue 2
   BK_FILL_CLEAR,

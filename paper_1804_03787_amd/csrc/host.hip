@@ -336,8 +336,8 @@ msgpm_status side_by_side(hipStream_t s, A&& on_caller, B&& on_second) {
   return st1 != MSGPM_OK ? st1 : st0;
 }
 
-msgpm_status run_lists(const Ctx& c) {
-  return check(timed(MSGPM_T_PM_LIST, c.s, [&] { return launch_pm_lists(c.P, c.w, c.s); }), "pm_list");
+msgpm_status run_lists(const Ctx& c, bool cleared = false) {
+  return check(timed(MSGPM_T_PM_LIST, c.s, [&] { return launch_pm_lists(c.P, c.w, cleared, c.s); }), "pm_list");
 }
 
 // A restricted half-sweep as two launches, launch(ident, stream): pixels with a
@@ -419,9 +419,7 @@ msgpm_status msgpm_features(const msgpm_params* p, const float* d_rgb1, const fl
     st = check(timed(MSGPM_T_FEATURES, c.s, [&] { return launch_histeq(c.P, c.w, d_rgb1, d_rgb2, c.s); }), "histeq");
     if (st != MSGPM_OK) return st;
   }
-  st = check(timed(MSGPM_T_FEATURES, c.s, [&] { return launch_features(c.P, c.w, d_rgb1, 0, c.s); }), "features");
-  if (st != MSGPM_OK) return st;
-  return check(timed(MSGPM_T_FEATURES, c.s, [&] { return launch_features(c.P, c.w, d_rgb2, 1, c.s); }), "features");
+  return check(timed(MSGPM_T_FEATURES, c.s, [&] { return launch_features(c.P, c.w, d_rgb1, d_rgb2, c.s); }), "features");
 }
 
 msgpm_status msgpm_init_state(const msgpm_params* p, const int32_t* d_init_nnf0, const int32_t* d_init_nnf1,
@@ -482,7 +480,7 @@ msgpm_status msgpm_fb_unassign(const msgpm_params* p, void* d_ws, void* stream) 
   Ctx c;
   msgpm_status st = open_ctx(p, d_ws, stream, &c);
   if (st != MSGPM_OK) return st;
-  return check(timed(MSGPM_T_FB, c.s, [&] { return launch_fb_unassign(c.P, c.w, c.s); }), "fb_unassign");
+  return check(timed(MSGPM_T_FB, c.s, [&] { return launch_fb_unassign(c.P, c.w, true, c.s); }), "fb_unassign");
 }
 
 msgpm_status msgpm_unique(const msgpm_params* p, void* d_ws, void* stream) {
@@ -504,7 +502,7 @@ msgpm_status msgpm_nnf_update(const msgpm_params* p, void* d_ws, int level, void
   msgpm_status st = open_ctx(p, d_ws, stream, &c);
   if (st != MSGPM_OK) return st;
   if ((st = check_level(c, level, 1)) != MSGPM_OK) return st;
-  return check(timed(MSGPM_T_NNF_UPDATE, c.s, [&] { return launch_nnf_update(c.P, c.w, level, c.s); }), "nnf_update");
+  return check(timed(MSGPM_T_NNF_UPDATE, c.s, [&] { return launch_nnf_update(c.P, c.w, level, 0, c.s); }), "nnf_update");
 }
 
 msgpm_status msgpm_finalize(const msgpm_params* p, void* d_ws, float* d_flow0, float* d_flow1, uint8_t* d_occ0,
@@ -532,8 +530,7 @@ msgpm_status solve_sequence(const Ctx& c, const float* d_rgb1, const float* d_rg
     if (s_ != MSGPM_OK) return s_;               \
   } while (0)
   if (c.P.histeq) RUN(timed(MSGPM_T_FEATURES, c.s, [&] { return launch_histeq(c.P, c.w, d_rgb1, d_rgb2, c.s); }), "histeq");
-  RUN(timed(MSGPM_T_FEATURES, c.s, [&] { return launch_features(c.P, c.w, d_rgb1, 0, c.s); }), "features");
-  RUN(timed(MSGPM_T_FEATURES, c.s, [&] { return launch_features(c.P, c.w, d_rgb2, 1, c.s); }), "features");
+  RUN(timed(MSGPM_T_FEATURES, c.s, [&] { return launch_features(c.P, c.w, d_rgb1, d_rgb2, c.s); }), "features");
   RUN(timed(MSGPM_T_INIT, c.s, [&] { return launch_init_state(c.P, c.w, d_init_nnf0, d_init_nnf1, c.s); }), "init_state");
   // the initial pass, its cost refresh folded into it
   if ((st = run_pm_pass(c, 0, 0)) != MSGPM_OK) return st;
@@ -544,12 +541,15 @@ msgpm_status solve_sequence(const Ctx& c, const float* d_rgb1, const float* d_rg
       RUN(timed(MSGPM_T_SYMMETRY, c.s, [&] { return launch_symmetry(c.P, c.w, l, stage, c.s); }), "symmetry");
       RUN(timed(MSGPM_T_ASSIGN, c.s, [&] { return launch_assign(c.P, c.w, l, stage, 2, c.s); }), "assign");
     }
-    RUN(timed(MSGPM_T_FB, c.s, [&] { return launch_fb_unassign(c.P, c.w, c.s); }), "fb_unassign");
-    if (c.P.cues & MSGPM_FLAG_CUE_UNIQUE) RUN(timed(MSGPM_T_FB, c.s, [&] { return launch_unique(c.P, c.w, c.s); }), "unique");
-    RUN(timed(MSGPM_T_NNF_UPDATE, c.s, [&] { return launch_nnf_update(c.P, c.w, l, c.s); }), "nnf_update");
+    // what the check leaves becomes the assignment in the NNF update, or before
+    // the cue that needs it
+    const bool unique = (c.P.cues & MSGPM_FLAG_CUE_UNIQUE) != 0;
+    RUN(timed(MSGPM_T_FB, c.s, [&] { return launch_fb_unassign(c.P, c.w, unique, c.s); }), "fb_unassign");
+    if (unique) RUN(timed(MSGPM_T_FB, c.s, [&] { return launch_unique(c.P, c.w, c.s); }), "unique");
+    RUN(timed(MSGPM_T_NNF_UPDATE, c.s, [&] { return launch_nnf_update(c.P, c.w, l, unique ? 0 : 1, c.s); }), "nnf_update");
     // the unassigned pixels' lists serve the whole restricted pass (its cost
     // refresh folded into it)
-    if ((st = run_lists(c)) != MSGPM_OK) return st;
+    if ((st = run_lists(c, true)) != MSGPM_OK) return st;
     if ((st = run_pm_pass(c, l + 1, 1)) != MSGPM_OK) return st;
   }
   if (c.P.fill_sweeps > 0) RUN(timed(MSGPM_T_FILL, c.s, [&] { return launch_fill(c.P, c.w, c.s); }), "fill");
@@ -754,12 +754,13 @@ std::vector<BatchStep> batch_schedule(const DevParams& P) {
       add(BK_ASSIGN, MSGPM_T_ASSIGN, l, stage, 2);
     }
     add(BK_FB, MSGPM_T_FB);
-    add(BK_COMMIT, MSGPM_T_FB);
-    if (P.cues & MSGPM_FLAG_CUE_UNIQUE)
+    const bool unique = (P.cues & MSGPM_FLAG_CUE_UNIQUE) != 0;
+    if (unique) {
+      add(BK_COMMIT, MSGPM_T_FB);
       for (int phase = 0; phase < 4; ++phase) add(BK_UNIQUE, MSGPM_T_FB, phase);
-    add(BK_NNF_UPDATE, MSGPM_T_NNF_UPDATE, l);
-    add(BK_ZERO_ACTIVE, MSGPM_T_PM_LIST);
-    for (int colour = 0; colour < 2; ++colour) add(BK_ACTIVE_LIST, MSGPM_T_PM_LIST, colour);
+    }
+    add(BK_NNF_UPDATE, MSGPM_T_NNF_UPDATE, l, unique ? 0 : 1);
+    add(BK_ACTIVE_LIST, MSGPM_T_PM_LIST);
     if (P.iters == 0) {
       add(BK_EVAL_COST_IDENT, MSGPM_T_EVAL_COST, 1);
       add(BK_EVAL_COST_PLANE, MSGPM_T_EVAL_COST, 1);
@@ -913,9 +914,7 @@ Plan make_plan(int n, const std::vector<DevParams>& P, const msgpm_tuning& t, in
     L.lds = lds;
     const int w = t.wg_per_cu[tune_class(st.kind)];
     L.persist = true;
-    if (st.kind == BK_ZERO_ACTIVE) {
-      L.grid = kXcds;
-    } else if (w == 0) {
+    if (w == 0) {
       L.grid = start;  // one workgroup per virtual workgroup
       L.persist = false;
     } else {
@@ -1158,7 +1157,8 @@ namespace {
 constexpr int kCohorts = MSGPM_SERVER_MAX_COHORTS;  // cohorts in flight at most (and server streams)
 // Limit on the launches of a served pipeline, counted as one per phase step
 // (served_launches), and those a region has room for: a batch makes fewer of
-// them for restricted half-sweeps, and one more per PatchMatch pass (moments).
+// them for restricted half-sweeps and their lists, and one more per PatchMatch
+// pass (moments).
 constexpr int kMaxLaunches = 4096;
 constexpr int kMaxMoments = 1 + MSGPM_MAX_LEVELS;
 

@@ -149,8 +149,10 @@ __global__ __launch_bounds__(kBlock) void k_heq_map(DevParams P, Ws w) {
                (unsigned)(P.W * P.H));
 }
 
-__global__ __launch_bounds__(kBlock) void k_features(DevParams P, Ws w, const float* __restrict__ rgb, int frame) {
-  features_body(rgb, P.W, P.H, P.C, P.fp16, heq_map(P, w, frame), heq_flat(P, w, frame),
+__global__ __launch_bounds__(kBlock) void k_features(DevParams P, Ws w, const float* __restrict__ rgb1,
+                                                     const float* __restrict__ rgb2) {
+  const int frame = blockIdx.y;
+  features_body(frame ? rgb2 : rgb1, P.W, P.H, P.C, P.fp16, heq_map(P, w, frame), heq_flat(P, w, frame),
                 const_cast<void*>(w.feat[frame]), blk_here());
 }
 
@@ -210,9 +212,9 @@ hipError_t launch_histeq(const DevParams& P, const Ws& w, const float* rgb1, con
   return hipGetLastError();
 }
 
-hipError_t launch_features(const DevParams& P, const Ws& w, const float* rgb, int frame, hipStream_t s) {
+hipError_t launch_features(const DevParams& P, const Ws& w, const float* rgb1, const float* rgb2, hipStream_t s) {
   const int n = P.W * P.H + 1;  // pixels plus the zero pad pixel
-  hipLaunchKernelGGL(k_features, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, P, w, rgb, frame);
+  hipLaunchKernelGGL(k_features, dim3((n + kBlock - 1) / kBlock, 2), dim3(kBlock), 0, s, P, w, rgb1, rgb2);
   return hipGetLastError();
 }
 

@@ -449,7 +449,8 @@ __device__ inline void pm_candidates_serial(const LaneCol<R, C, IDENT>& L, const
 // in two lists sharing one buffer per direction: pixels with a region plane
 // from the front (distorted patches), pixels without one from the back
 // (identity patches: the update of the initial pass, without a plane
-// candidate).  Each workgroup appends the pixels of its span (row-major) at
+// candidate).  The first half of a direction's workgroups lists colour 0, the
+// second colour 1.  Each workgroup appends the pixels of its span at
 // positions taken from the two counters; the order of the spans varies between
 // runs, and the update of a pixel does not depend on it.
 // ---------------------------------------------------------------------------
@@ -457,20 +458,14 @@ __global__ void k_zero_active(Ws w) {
   if (threadIdx.x < 8) w.act_count[threadIdx.x] = 0u;
 }
 
-// batched: each workgroup takes items blockIdx.x, blockIdx.x + gridDim.x, ...
-__global__ void kb_zero_active(const uint8_t* __restrict__ tab, int k) {
-  const BatchView V = batch_view(tab, k);
-  for (int i = blockIdx.x; i < V.n; i += gridDim.x)
-    if (threadIdx.x < 8) V.pd[V.it[i].pair].w.act_count[threadIdx.x] = 0u;
-}
-
 constexpr int kListSpan = 4;  // pixels of the colour per thread of k_active_list
 
-__device__ __forceinline__ void active_list_body(const DevParams& P, const Ws& w, Blk bk, int colour) {
+__device__ __forceinline__ void active_list_body(const DevParams& P, const Ws& w, Blk bk) {
   constexpr int NS = kListSpan * (kBlock / kWave);
   __shared__ int s_cnt[2][NS];
   __shared__ unsigned s_base[2];
-  const int dir = bk.y;
+  const int dir = bk.y, half = bk.nx >> 1, colour = bk.x >= half ? 1 : 0;
+  bk.x -= colour * half;
   const int W = P.W, H = P.H, Wh = (W + 1) >> 1, ntx = (W + 15) >> 4;
   const unsigned cap = (unsigned)Wh * (unsigned)H;
   const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
@@ -521,8 +516,8 @@ __device__ __forceinline__ void active_list_body(const DevParams& P, const Ws& w
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_active_list(DevParams P, Ws w, int colour) {
-  active_list_body(P, w, blk_here(), colour);
+__global__ __launch_bounds__(kBlock) void k_active_list(DevParams P, Ws w) {
+  active_list_body(P, w, blk_here());
 }
 
 __global__ __launch_bounds__(kBlock) void kb_active_list(const uint8_t* __restrict__ tab, int k, BArgs A) {
@@ -531,7 +526,7 @@ __global__ __launch_bounds__(kBlock) void kb_active_list(const uint8_t* __restri
   const Item* __restrict__ it = V.it;
   const int n = V.n, total = V.total;
   for_each_item<true>(it, n, total, [&](int i, Blk bk) {
-    active_list_body(pd[it[i].pair].P, pd[it[i].pair].w, bk, A.a[0]);
+    active_list_body(pd[it[i].pair].P, pd[it[i].pair].w, bk);
   });
 }
 
@@ -676,23 +671,24 @@ static hipError_t dispatch_restricted(const DevParams& P, const Ws& w, int colou
   return pm_launch<R, C, FP16, false>(P, w, colour, iter, slot, mode, s);
 }
 
-// Workgroups of k_active_list for one direction and colour: the tiles cover no
-// fewer pixels than the rows.
+// Workgroups of k_active_list for both colours of a direction: the tiles cover
+// no fewer pixels than the rows.
 static int list_blocks(const DevParams& P) {
   const int tiles = ((P.W + 15) >> 4) * ((P.H + 7) >> 3), per = kListSpan * kBlock / 64;
-  return (tiles + per - 1) / per;
+  return 2 * ((tiles + per - 1) / per);
 }
 
 // The lists of both colours; they hold for every half-sweep of a restricted
 // pass (assignment and region planes do not change during it).
-hipError_t launch_pm_lists(const DevParams& P, const Ws& w, hipStream_t s) {
-  hipLaunchKernelGGL(k_zero_active, dim3(1), dim3(kWave), 0, s, w);
-  hipError_t e = hipGetLastError();
-  for (int colour = 0; colour < 2 && e == hipSuccess; ++colour) {
-    hipLaunchKernelGGL(k_active_list, dim3(list_blocks(P), 2), dim3(kBlock), 0, s, P, w, colour);
-    e = hipGetLastError();
+// cleared: their counts are 0 already (k_nnf_update).
+hipError_t launch_pm_lists(const DevParams& P, const Ws& w, bool cleared, hipStream_t s) {
+  if (!cleared) {
+    hipLaunchKernelGGL(k_zero_active, dim3(1), dim3(kWave), 0, s, w);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  return e;
+  hipLaunchKernelGGL(k_active_list, dim3(list_blocks(P), 2), dim3(kBlock), 0, s, P, w);
+  return hipGetLastError();
 }
 
 // Workgroups of one direction of a cost refresh: tiles, or (mode 1) runs of both
@@ -762,10 +758,6 @@ static hipError_t dispatch_batched(int kind, const uint8_t* tab, int k, int ngri
 
 hipError_t launch_batched_pm(int kind, const DevParams& P0, const uint8_t* tab, int k, int grid, BArgs A,
                              bool persist, hipStream_t s) {
-  if (kind == BK_ZERO_ACTIVE) {
-    hipLaunchKernelGGL(kb_zero_active, dim3(grid), dim3(kWave), 0, s, tab, k);
-    return hipGetLastError();
-  }
   if (kind == BK_ACTIVE_LIST) {
     hipLaunchKernelGGL(kb_active_list, dim3(grid, 2), dim3(kBlock), 0, s, tab, k, A);
     return hipGetLastError();
@@ -781,8 +773,6 @@ int pm_batch_blocks(int kind, const DevParams& P, const int* a) {
     case BK_EVAL_COST_IDENT:
     case BK_EVAL_COST_PLANE:
       return cost_blocks(P, a ? a[0] : 0);
-    case BK_ZERO_ACTIVE:
-      return 1;
     case BK_ACTIVE_LIST:
       return list_blocks(P);
     default:
