@@ -342,7 +342,7 @@ hipError_t launch_batched_pm(int kind, const DevParams& P0, const uint8_t* tab, 
 hipError_t launch_batched_search(int kind, const DevParams& P0, const uint8_t* tab, int k, int grid, BArgs A,
                                  bool persist, hipStream_t s);
 int search_batch_blocks(int kind, const DevParams& P);
-hipError_t launch_batched_planes(int kind, const uint8_t* tab, int k, int grid, size_t lds, BArgs A, hipStream_t s);
+hipError_t launch_batched_planes(int kind, const DevParams& P0, const uint8_t* tab, int k, int grid, size_t lds, BArgs A, hipStream_t s);
 size_t ransac_smem_bytes(const DevParams& P, int level);
 // The same for a full B x B window (any frame of at least that size).
 size_t ransac_smem_bytes_window(int B);

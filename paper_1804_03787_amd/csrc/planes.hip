@@ -1062,13 +1062,12 @@ __global__ __launch_bounds__(kBlock) void kb_assign(const uint8_t* __restrict__ 
 
 // ---------------------------------------------------------------------------
 // Plane symmetry: one workgroup per (window, direction).  A pixel is a chain of
-// dependent loads and FP64 divisions; of a single pair the workgroups take eight
-// pixels per thread, so that large windows fill the chip and small ones do not
+// dependent loads and FP64 divisions; the workgroups take eight pixels
+// per thread, so that large windows fill the chip and small ones do not
 // spend their time on opening and closing workgroups.  Stage 1 with 256 threads
 // and so: 64x64 at 1024x436 67 us -> 50 us, 16x16 111 us -> 65 us (at 2048x872
 // 128x128 177 us -> 74 us, 16x16 407 us -> 203 us); four pixels per thread take
-// 300 us for 64x64 at 2048x872 instead of 171.  A batch fills the chip and
-// keeps workgroups of kBlock.
+// 300 us for 64x64 at 2048x872 instead of 171.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void symmetry_body(const DevParams& P, const Ws& w, Blk bk, int level, int stage) {
   __shared__ int s_rk, s_pass, s_rin;
@@ -1129,7 +1128,7 @@ __global__ __launch_bounds__(kSymBlock) void k_symmetry(DevParams P, Ws w, int l
   symmetry_body(P, w, blk_here(), level, stage);
 }
 
-__global__ __launch_bounds__(kBlock) void kb_symmetry(const uint8_t* __restrict__ tab, int k, BArgs A) {
+__global__ __launch_bounds__(kSymBlock) void kb_symmetry(const uint8_t* __restrict__ tab, int k, BArgs A) {
   const BatchView V = batch_view(tab, k);
   const PairDesc* __restrict__ pd = V.pd;
   const Item* __restrict__ it = V.it;
@@ -1460,11 +1459,14 @@ hipError_t launch_assign(const DevParams& P, const Ws& w, int level, int stage, 
   return hipGetLastError();
 }
 
+static dim3 symmetry_block(const DevParams& P, int level) {
+  const int B = P.block[level], threads = (B * B / 8 + kWave - 1) / kWave * kWave;
+  return dim3(threads < kWave ? kWave : (threads > kSymBlock ? kSymBlock : threads));
+}
+
 hipError_t launch_symmetry(const DevParams& P, const Ws& w, int level, int stage, hipStream_t s) {
-  const int B = P.block[level];
-  int threads = (B * B / 8 + kWave - 1) / kWave * kWave;
-  threads = threads < kWave ? kWave : (threads > kSymBlock ? kSymBlock : threads);
-  hipLaunchKernelGGL(k_symmetry, dim3(P.nbx[level] * P.nby[level], 2), dim3(threads), 0, s, P, w, level, stage);
+  hipLaunchKernelGGL(k_symmetry, dim3(P.nbx[level] * P.nby[level], 2), symmetry_block(P, level), 0, s, P, w, level,
+                     stage);
   return hipGetLastError();
 }
 
@@ -1506,7 +1508,7 @@ hipError_t launch_finalize(const DevParams& P, const Ws& w, float* flow0, float*
   return hipGetLastError();
 }
 
-hipError_t launch_batched_planes(int kind, const uint8_t* tab, int k, int ngrid, size_t lds, BArgs A,
+hipError_t launch_batched_planes(int kind, const DevParams& P0, const uint8_t* tab, int k, int ngrid, size_t lds, BArgs A,
                                  hipStream_t s) {
   const dim3 grid(ngrid, batch_grid_y(kind)), block(kBlock);
   switch (kind) {
@@ -1525,7 +1527,8 @@ hipError_t launch_batched_planes(int kind, const uint8_t* tab, int k, int ngrid,
       hipLaunchKernelGGL(kb_assign, grid, block, 0, s, tab, k, A);
       break;
     case BK_SYMMETRY:
-      hipLaunchKernelGGL(kb_symmetry, grid, block, 0, s, tab, k, A);
+      // by the first pair's windows: any size gives the same result
+      hipLaunchKernelGGL(kb_symmetry, grid, symmetry_block(P0, A.a[0]), 0, s, tab, k, A);
       break;
     case BK_FB:
       hipLaunchKernelGGL(kb_fb, grid, block, 0, s, tab, k, A);
@@ -1610,7 +1613,7 @@ hipError_t launch_batched(int kind, const DevParams& P0, const uint8_t* tab, int
     case BK_PM_RESTRICTED:
       return launch_batched_search(kind, P0, tab, k, grid, A, persist, s);
     default:
-      return launch_batched_planes(kind, tab, k, grid, lds, A, s);
+      return launch_batched_planes(kind, P0, tab, k, grid, lds, A, s);
   }
 }
 
