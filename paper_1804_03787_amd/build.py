@@ -14,7 +14,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libmsgpm.so")
-SOURCES = ["host.hip", "init.hip", "patchmatch.hip", "planes.hip", "search.hip"]
+SOURCES = ["host.hip", "init.hip", "patchmatch.hip", "planes.hip"]
 CEILING_OUT = os.path.join(HERE, "libmsgpm_ceiling.so")
 CEILING_SOURCE = "ceiling.hip"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

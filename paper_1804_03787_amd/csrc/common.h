@@ -237,7 +237,7 @@ __host__ __device__ inline void cover_range(int n, int B, int nb, int c, int& lo
   if (hi > nb - 1) hi = nb - 1;
 }
 
-// Half-sweeps of a whole pass (search.hip): what a launch is told.  SM_FIRST:
+// Half-sweeps of a whole pass (search.h): what a launch is told.  SM_FIRST:
 // the pass's first half-sweep of the colour, which computes the pixels' current
 // costs and ignores what earlier half-sweeps noted; SM_LAST: the last one of the
 // last pass, which leaves no notes behind.  Those of an earlier pass stay in win
@@ -245,7 +245,7 @@ __host__ __device__ inline void cover_range(int n, int B, int nb, int c, int& lo
 // last half-sweep of the second colour still needs the first colour's (without
 // them it offers every neighbour again, at 1024x436 half as long again).
 enum { SM_RESTRICTED = 1, SM_FIRST = 2, SM_LAST = 4 };
-// The largest note (search.hip) as an int, below any assignment or filling.
+// The largest note (search.h) as an int, below any assignment or filling.
 constexpr int32_t kLastNote = (int32_t)0x83ffffff;
 
 // Workgroups over which a half-sweep of one pair is spread before one takes more

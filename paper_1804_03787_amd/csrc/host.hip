@@ -379,7 +379,7 @@ int search_mode(const DevParams& P, int slot, int it) {
 // pixels' costs before their candidates; a pass without half-sweeps runs it
 // on its own.  The half-sweeps of a pass note in win what later ones of it need
 // not try again, and bound costs by moments kept over twin and tloss
-// (search.hip), so they run here alone: a half-sweep called by itself
+// (search.h), so they run here alone: a half-sweep called by itself
 // (run_halfsweep) leaves both as they are.
 msgpm_status run_pm_pass(const Ctx& c, int slot, int restricted) {
   if (c.P.iters == 0)

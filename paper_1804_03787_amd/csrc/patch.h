@@ -1,5 +1,5 @@
 // Warped-patch SSD of one pixel's lane group: the device functions shared by the
-// PatchMatch kernels of patchmatch.hip and search.hip.
+// PatchMatch kernels of patchmatch.hip and search.h.
 #pragma once
 
 #include "common.h"

@@ -26,6 +26,7 @@
 // Sec. 3.1) runs as red-black Jacobi half-sweeps: a pixel reads only the other
 // colour's offsets, so a half-sweep is order-free.
 #include "patch.h"
+#include "search.h"
 
 #pragma clang fp contract(off)
 

@@ -36,6 +36,8 @@
 // work, sorted by their number of candidates so that the groups of a wave finish
 // together, go to the lane groups of its four waves.  The two phases run twice,
 // for propagation and for random search, and meet in LDS.
+#pragma once
+
 #include "patch.h"
 
 #pragma clang fp contract(off)
