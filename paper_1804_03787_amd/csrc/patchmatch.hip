@@ -35,15 +35,25 @@ namespace msgpm {
 // ---------------------------------------------------------------------------
 // Cost refresh: cost[p] = C(p, p + v_p, H_p) for the selected pixels.
 //
-// A workgroup owns kCostSlots pixels: a tile of the frame (whose patches
+// A workgroup owns up to kCostSlots pixels: a tile of the frame (whose patches
 // overlap), or a run of a list.  One lane per pixel takes its target and its
 // plane's local motion (FP64) into LDS; then the lane groups take the selected
 // pixels in turn, so that none sits idle for a pixel without a plane.  One
 // group per pixel of a row of the frame instead, each of its lanes computing the
 // motion, took 590 us for the final refresh of a 1280x544 pair (with the
-// outputs), 464 us now.
+// outputs), with its three waves per SIMD (FP16 four) 428 us now, of a
+// sparsely assigned 512x384 pair 47 us then and 53 us now.
 // ---------------------------------------------------------------------------
 constexpr int kCostSlots = 128, kCostTileW = 16;
+
+// Pixels of a workgroup: fewer where a frame would leave compute units without
+// one.  Unassigned pixels (FP32, mode 1, with the lists) with 128, 64 and 32 pixels:
+// 128x96 38, 33 and 26 us, 320x240 68, 53 and 57 us, 512x384 115, 102 and 111 us;
+// assigned ones of a 512x384 pair (mode 2, with the outputs) 57, 63 and 81 us.
+__host__ __device__ inline int cost_slots(const DevParams& P) {
+  const int n = P.W * P.H;
+  return n >= 98304 ? kCostSlots : (n >= 32768 ? 64 : 32);
+}
 
 struct CostLds {
   int pix[kCostSlots], tgt[kCostSlots];  // x | y << 16
@@ -62,7 +72,8 @@ __device__ __forceinline__ void eval_cost_body(const DevParams& P, const Ws& w, 
   const int dir = bk.y;
   const int W = P.W, H = P.H;
   // this lane's pixel
-  bool act = t < kCostSlots;
+  const int slots = cost_slots(P);
+  bool act = t < slots;
   int x = 0, y = 0;
   if (mode == 1) {
     // the unassigned pixels, from the restricted pass's lists (both colours):
@@ -70,10 +81,10 @@ __device__ __forceinline__ void eval_cost_body(const DevParams& P, const Ws& w, 
     // over the front lists; each colour takes its own run of workgroups
     const unsigned c0 = w.act_count[2 * (2 * dir) + (IDENT ? 1 : 0)];
     const unsigned c1 = w.act_count[2 * (2 * dir + 1) + (IDENT ? 1 : 0)];
-    const int nb0 = (int)((c0 + kCostSlots - 1) / kCostSlots), nb1 = (int)((c1 + kCostSlots - 1) / kCostSlots);
+    const int nb0 = (int)((c0 + slots - 1) / slots), nb1 = (int)((c1 + slots - 1) / slots);
     if (bk.x >= nb0 + nb1) return;
     const int colour = bk.x < nb0 ? 0 : 1;
-    const unsigned i = (unsigned)xcd_remap(colour ? bk.x - nb0 : bk.x, colour ? nb1 : nb0) * kCostSlots + t;
+    const unsigned i = (unsigned)xcd_remap(colour ? bk.x - nb0 : bk.x, colour ? nb1 : nb0) * slots + t;
     act = act && i < (colour ? c1 : c0);
     const unsigned cap = (unsigned)((W + 1) >> 1) * (unsigned)H;
     const int q = act ? w.act[2 * dir + colour][IDENT ? cap - 1u - i : i] : 0;
@@ -82,7 +93,7 @@ __device__ __forceinline__ void eval_cost_body(const DevParams& P, const Ws& w, 
   } else {
     const int ntx = (W + kCostTileW - 1) / kCostTileW, b = xcd_remap(bk.x, bk.nx);
     x = b % ntx * kCostTileW + t % kCostTileW;
-    y = b / ntx * (kCostSlots / kCostTileW) + t / kCostTileW;
+    y = b / ntx * (slots / kCostTileW) + t / kCostTileW;
     act = act && x < W && y < H;
   }
   const int p = y * W + x;
@@ -149,13 +160,18 @@ __device__ __forceinline__ void eval_cost_body(const DevParams& P, const Ws& w, 
   count_evals<true>(w.counters, 2 + dir, act ? 1u : 0u);
 }
 
+// Waves per SIMD the registers of distorted patches are held to: a final refresh
+// of a 1024x436 pair with the outputs takes 182 us at the compiler's own choice of
+// 2 (FP16 3: 116 us), 166 us at 3 (108 us at 4) and 227 us at 4, with spills.
+constexpr int cost_waves(bool fp16, bool ident) { return ident ? 1 : (fp16 ? 4 : 3); }
+
 template <int R, int C, bool FP16, bool IDENT>
-__global__ __launch_bounds__(kBlock) void k_eval_cost(DevParams P, Ws w, int mode) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(cost_waves(FP16, IDENT)))) void k_eval_cost(DevParams P, Ws w, int mode) {
   eval_cost_body<R, C, FP16, IDENT>(P, w, blk_here(), mode);
 }
 
 template <int R, int C, bool FP16, bool IDENT, bool LOOP>
-__global__ __launch_bounds__(kBlock) void kb_eval_cost(const uint8_t* __restrict__ tab, int k, BArgs A) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(cost_waves(FP16, IDENT)))) void kb_eval_cost(const uint8_t* __restrict__ tab, int k, BArgs A) {
   const BatchView V = batch_view(tab, k);
   const PairDesc* __restrict__ pd = V.pd;
   const Item* __restrict__ it = V.it;
@@ -695,8 +711,8 @@ hipError_t launch_pm_lists(const DevParams& P, const Ws& w, bool cleared, hipStr
 // Workgroups of one direction of a cost refresh: tiles, or (mode 1) runs of both
 // colours' lists.
 static int cost_blocks(const DevParams& P, int mode) {
-  if (mode == 1) return 2 * ((((P.W + 1) >> 1) * P.H + kCostSlots - 1) / kCostSlots);
-  constexpr int th = kCostSlots / kCostTileW;
+  const int slots = cost_slots(P), th = slots / kCostTileW;
+  if (mode == 1) return 2 * ((((P.W + 1) >> 1) * P.H + slots - 1) / slots);
   return ((P.W + kCostTileW - 1) / kCostTileW) * ((P.H + th - 1) / th);
 }
 
