@@ -40,9 +40,9 @@ namespace msgpm {
 // plane's local motion (FP64) into LDS; then the lane groups take the selected
 // pixels in turn, so that none sits idle for a pixel without a plane.  One
 // group per pixel of a row of the frame instead, each of its lanes computing the
-// motion, took 590 us for the final refresh of a 1280x544 pair (with the
-// outputs), with its three waves per SIMD (FP16 four) 428 us now, of a
-// sparsely assigned 512x384 pair 47 us then and 53 us now.
+// motion: the final refresh of a 1280x544 pair with the outputs took 590 us, now
+// 428 (FP16 546, now 290); where few pixels are assigned, 512x384, 47 us, now 53
+// (FP16 36, now 37).
 // ---------------------------------------------------------------------------
 constexpr int kCostSlots = 128, kCostTileW = 16;
 
