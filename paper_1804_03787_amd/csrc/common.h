@@ -49,7 +49,8 @@ struct Ws {
   unsigned* heq;          // histograms [2][256], then FP32 maps [2][256], then flags [2]
   int32_t* act[4];        // pixels a restricted half-sweep updates, [direction][colour]
   unsigned* act_count;    // list lengths [direction][colour][with region plane, without], then
-                          // the filling's ring of 4 counts per direction
+                          // 8 words: the scale and rounding term of the patch moments (search.h)
+                          // during a PatchMatch pass, the filling's ring of 4 counts per direction
 };
 
 // Batched launches: one launch covers the same phase of several frame pairs.

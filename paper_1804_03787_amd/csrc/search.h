@@ -105,9 +105,20 @@ __device__ inline int xy_y(int v) { return (int)((unsigned)v >> 16); }
 // most b K from the undistorted one, K^2 the sum of |d|^2 (hx^2 + hy^2) over
 // the patch.  The last byte of a pixel holds K, rounded up, in units of
 // kRough / scale; 255: larger, or not known.
+//
+// That is the exact interpolation.  In FP32 (u = 2^-24) the four weights are off by
+// at most 3u of their value, and the sums of four terms that stay within the
+// largest corner M add 4u M, so that a sample is off by under 7.01u M, and the
+// patch by sqrt(3) T as much.  In units that is kRounding M / half range, whatever
+// T.  M is bounded by the centre and kFar half ranges; where a tap could read a
+// pixel farther from the centre, K counts as not known.  On frames that span
+// their range the term is under 0.003 units; past a level of 30000 half ranges
+// it outgrows the other slack.
 constexpr int kMomW = 32, kMomH = 8;  // pixels of a workgroup's tile
 constexpr float kMomSlack = 3.3267f;  // sqrt(11) + 0.01
 constexpr float kRough = 4.0f;
+constexpr float kFar = 16.0f;
+constexpr float kRounding = 1.15e-4f;  // 127 / 0.8 sqrt(3) 7.01 u
 
 template <int R>
 struct MomLds {
@@ -169,7 +180,10 @@ __device__ __forceinline__ void moments_body(const DevParams& P, const Ws& w, Bl
   // sample, or values that are not finite): scale 0, which bounds nothing.
   const bool usable = half > 1e-15f && half < 1e15f;
   const float scale = usable ? 127.0f / (0.8f * (float)T * half) : 0.0f;
-  if (bk.x == 0 && f == 0 && t == 0) w.act_count[8] = __float_as_uint(scale);
+  if (bk.x == 0 && f == 0 && t == 0) {
+    w.act_count[8] = __float_as_uint(scale);
+    w.act_count[9] = __float_as_uint(usable ? kRounding * (fabsf(centre) / half + kFar) : 0.f);
+  }
   const int ntx = (W + kMomW - 1) / kMomW;
   const int x0 = (bk.x % ntx) * kMomW, y0 = (bk.x / ntx) * kMomH;
   const float cut = 2.0f * half;
@@ -182,21 +196,22 @@ __device__ __forceinline__ void moments_body(const DevParams& P, const Ws& w, Bl
   __syncthreads();
   for (int i = t; i < TW * TH; i += kBlock) {
     const int ly = i / TW + 1, lx = i % TW + 1;
-    float e = 0.f;
+    float e = 0.f, far = 0.f;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       float hx = 0.f;
 #pragma unroll
       for (int d = -1; d <= 1; ++d) {
-        const float m = S.v[c][ly + d][lx];
-        hx = fmaxf(hx, fmaxf(fabsf(S.v[c][ly + d][lx - 1] - m), fabsf(S.v[c][ly + d][lx + 1] - m)));
+        const float m = S.v[c][ly + d][lx], l = S.v[c][ly + d][lx - 1], r = S.v[c][ly + d][lx + 1];
+        hx = fmaxf(hx, fmaxf(fabsf(l - m), fabsf(r - m)));
+        far = fmaxf(fmaxf(far, fabsf(m - centre)), fmaxf(fabsf(l - centre), fabsf(r - centre)));
       }
       const float m = S.v[c][ly][lx];
       const float hy = fmaxf(fabsf(S.v[c][ly - 1][lx] - m), fabsf(S.v[c][ly + 1][lx] - m));
       hx *= scale;
       e = fmaf(hx, hx, fmaf(hy * scale, hy * scale, e));
     }
-    S.h2[ly - 1][lx - 1] = e;
+    S.h2[ly - 1][lx - 1] = far > kFar * half ? __builtin_huge_valf() : e;
   }
   for (int i = t; i < 3 * TH * kMomW; i += kBlock) {
     const int lx = i % kMomW, ly = (i / kMomW) % TH, c = i / (kMomW * TH);
@@ -302,6 +317,7 @@ __device__ inline int moments_norm2(u32x3 a) { return dot4(a.x, a.x, dot4(a.y, a
 struct Bound {
   u32x3 src;    // the pixel's moments, without the last byte
   float shift;  // b of the pixel's distortion times kRough; infinite: no bound
+  float round;  // units by which rounded samples may move a distorted patch
   float unit2;  // squared length of a unit, less what the cost may be under the exact SSD
 };
 
@@ -328,7 +344,7 @@ __device__ inline float cost_bound(const Bound& f, const Moments& M2, int p) {
   t.z &= 0xffffffu;
   const int dot = dot4(f.src.x, t.x, dot4(f.src.y, t.y, dot4(f.src.z, t.z, 0)));
   const float d = sqrtf((float)(moments_norm2(f.src) + moments_norm2(t) - 2 * dot));
-  const float less = f.shift > 0.f ? f.shift * (rough == 255u ? __builtin_huge_valf() : (float)rough) : 0.f;
+  const float less = f.shift > 0.f ? fmaf(f.shift, rough == 255u ? __builtin_huge_valf() : (float)rough, f.round) : 0.f;
   const float v = d - kMomSlack - less;
   return v > 0.f ? v * v * f.unit2 : 0.f;  // less infinite or not a number: 0
 }
@@ -498,7 +514,8 @@ struct SlotMap {
 // the lanes of k == 0 also load the pixel's own state.
 template <int R, bool IDENT>
 __device__ inline void open_slot(const DevParams& P, const Ws& w, int dir, SearchLds& S, const SlotMap& M, int sl, int k,
-                                 bool first, const Moments& M1, const Moments& M2, float unit2, unsigned& evals) {
+                                 bool first, const Moments& M1, const Moments& M2, float unit2, float round,
+                                 unsigned& evals) {
   const int W = P.W, H = P.H;
   int x, y;
   if (!M.at(sl, x, y)) {
@@ -515,6 +532,7 @@ __device__ inline void open_slot(const DevParams& P, const Ws& w, int dir, Searc
   Bound f{};
   if (k == 0 || first) f.src = M1.at(p);
   f.unit2 = unit2;
+  f.round = round;
   const int best0 = pack_xy(x + off_dx(v0), y + off_dy(v0));
   int tp = -1;
   if (k == 0) {
@@ -574,7 +592,7 @@ __device__ inline void open_slot(const DevParams& P, const Ws& w, int dir, Searc
 // the positions noted by this lane for the slot.
 template <bool IDENT>
 __device__ inline void offer_random(const DevParams& P, SearchLds& S, int sl, int k, const Moments& M2, float unit2,
-                                    unsigned& mine, unsigned& evals) {
+                                    float round, unsigned& mine, unsigned& evals) {
   if (S.pix[sl] < 0) return;
   const int b = S.best[sl], bx = xy_x(b), by = xy_y(b);
   const int32_t v = S.tgt[k][sl];
@@ -592,7 +610,7 @@ __device__ inline void offer_random(const DevParams& P, SearchLds& S, int sl, in
     atomicOr(&S.tried[sl], bit);
     if (b == S.best0[sl] && (S.memo[sl] & bit)) return;
   }
-  const Bound f{u32x3{S.src[0][sl], S.src[1][sl], S.src[2][sl]}, IDENT ? 0.f : S.shift[sl], unit2};
+  const Bound f{u32x3{S.src[0][sl], S.src[1][sl], S.src[2][sl]}, IDENT ? 0.f : S.shift[sl], round, unit2};
   const float lb = cost_bound(f, M2, ty * P.W + tx);
   if (lb >= S.bc[sl]) return;
   S.tgt[k][sl] = pack_xy(tx, ty);
@@ -655,7 +673,7 @@ __device__ __forceinline__ void search_body(const DevParams& P, const Ws& w, Sea
   const int nb = M.rows ? bk.nx : (int)((M.cnt + M.run - 1) / M.run), np = M.run;
   if (bk.x >= nb) return;
   M.b = xcd_remap(bk.x, nb);
-  const float unit2 = bound_unit2(__uint_as_float(w.act_count[8]));
+  const float unit2 = bound_unit2(__uint_as_float(w.act_count[8])), round = __uint_as_float(w.act_count[9]);
   const Moments M1 = moments_buf(w, dir, W * H), M2 = moments_buf(w, 1 - dir, W * H);
   const uint64_t w3 = rng_word3(2, dir, slot, 0);
   unsigned evals = 0, tap_rows = 0;
@@ -668,7 +686,7 @@ __device__ __forceinline__ void search_body(const DevParams& P, const Ws& w, Sea
   __syncthreads();
   // the neighbours' candidates, and the draws while their loads are on the way
   each_candidate(np, 4, [&](int sl, int k) {
-    open_slot<R, IDENT>(P, w, dir, S, M, sl, k, first, M1, M2, unit2, evals);
+    open_slot<R, IDENT>(P, w, dir, S, M, sl, k, first, M1, M2, unit2, round, evals);
   });
   each_candidate(np, P.nk, [&](int sl, int k) {
     int x, y;
@@ -681,7 +699,7 @@ __device__ __forceinline__ void search_body(const DevParams& P, const Ws& w, Sea
       unsigned mine = 0;
       each_candidate(np, P.nk, [&](int sl, int k) {
         if (np != kSlots) mine = 0;  // another slot
-        offer_random<IDENT>(P, S, sl, k, M2, unit2, mine, evals);
+        offer_random<IDENT>(P, S, sl, k, M2, unit2, round, mine, evals);
       });
       __syncthreads();
     }
