@@ -294,14 +294,17 @@ static int moments_blocks(const DevParams& P) {
   return ((P.W + kMomW - 1) / kMomW) * ((P.H + kMomH - 1) / kMomH);
 }
 
-// One frame's moments through a buffer resource (32-bit byte offsets: 12 bytes
-// for each of at most 2^28 pixels).
+// One frame's moments through a buffer resource: 32-bit byte offsets, unsigned, as
+// the 12 bytes of each of at most 2^28 pixels (FP16 RGB records of 2 GiB) pass
+// 2 GiB from pixel 178956971 on.
+__host__ __device__ constexpr uint32_t moment_offset(int p) { return (uint32_t)p * 12u; }
+static_assert(moment_offset((1 << 28) - 1) == 3221225460u, "offsets of the largest frame");
 struct Moments {
   __amdgpu_buffer_rsrc_t r;
-  __device__ inline u32x3 at(int p) const { return __builtin_amdgcn_raw_buffer_load_b96(r, p * 12, 0, 0); }
+  __device__ inline u32x3 at(int p) const { return __builtin_amdgcn_raw_buffer_load_b96(r, (int)moment_offset(p), 0, 0); }
 };
 __device__ inline Moments moments_buf(const Ws& w, int f, int n) {
-  return Moments{__builtin_amdgcn_make_buffer_rsrc(w.twin[f], (short)0, (int)((unsigned)n * 12u), 0x00020000)};
+  return Moments{__builtin_amdgcn_make_buffer_rsrc(w.twin[f], (short)0, (int)moment_offset(n), 0x00020000)};
 }
 
 __device__ inline int dot4(uint32_t a, uint32_t b, int c) {
