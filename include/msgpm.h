@@ -497,7 +497,8 @@ enum {
   MSGPM_T_FB = 8,
   MSGPM_T_NNF_UPDATE = 9,
   MSGPM_T_FINALIZE = 10,
-  MSGPM_T_PM_LIST = 11,            /* pixel lists of the restricted half-sweeps */
+  MSGPM_T_PM_LIST = 11,            /* what half-sweeps are prepared with: pixel lists of the restricted
+                                      ones, patch moments of the whole-pipeline calls' passes */
   MSGPM_T_PM_RESTRICTED_IDENT = 12, /* restricted half-sweeps, pixels without one (identity patches) */
   MSGPM_T_FILL = 13,               /* filling by model propagation */
   MSGPM_TIMER_KINDS = 14

@@ -103,7 +103,7 @@ Timer g_timer;
 const char* const kPhaseNames[MSGPM_TIMER_KINDS] = {
     "msgpm features", "msgpm init", "msgpm eval_cost", "msgpm pm initial pass", "msgpm pm restricted (distorted)",
     "msgpm ransac", "msgpm assign", "msgpm symmetry", "msgpm fb", "msgpm nnf_update", "msgpm finalize",
-    "msgpm pm lists", "msgpm pm restricted (identity)", "msgpm fill"};
+    "msgpm pm lists and moments", "msgpm pm restricted (identity)", "msgpm fill"};
 
 struct Range {
   bool on;
@@ -384,7 +384,7 @@ int search_mode(const DevParams& P, int slot, int it) {
 msgpm_status run_pm_pass(const Ctx& c, int slot, int restricted) {
   if (c.P.iters == 0)
     return check(timed(MSGPM_T_EVAL_COST, c.s, [&] { return launch_eval_cost(c.P, c.w, restricted, c.s); }), "eval_cost");
-  msgpm_status st = check(timed(MSGPM_T_FEATURES, c.s, [&] { return launch_moments(c.P, c.w, c.s); }), "moments");
+  msgpm_status st = check(timed(MSGPM_T_PM_LIST, c.s, [&] { return launch_moments(c.P, c.w, c.s); }), "moments");
   for (int it = 0; it < c.P.iters && st == MSGPM_OK; ++it)
     for (int colour = 0; colour < 2 && st == MSGPM_OK; ++colour) {
       const int mode = search_mode(c.P, slot, it);
@@ -742,7 +742,7 @@ std::vector<BatchStep> batch_schedule(const DevParams& P) {
   // cost refreshes are folded into the first half-sweep of each colour (run
   // alone when a pass has none)
   if (P.iters == 0) add(BK_EVAL_COST_IDENT, MSGPM_T_EVAL_COST, 0);
-  if (P.iters > 0) add(BK_MOMENTS, MSGPM_T_FEATURES);
+  if (P.iters > 0) add(BK_MOMENTS, MSGPM_T_PM_LIST);
   for (int it = 0; it < P.iters; ++it)
     for (int colour = 0; colour < 2; ++colour)
       add(BK_PM_INIT, MSGPM_T_PM_INIT, colour, it, 0, search_mode(P, 0, it));
@@ -765,7 +765,7 @@ std::vector<BatchStep> batch_schedule(const DevParams& P) {
       add(BK_EVAL_COST_IDENT, MSGPM_T_EVAL_COST, 1);
       add(BK_EVAL_COST_PLANE, MSGPM_T_EVAL_COST, 1);
     }
-    if (P.iters > 0) add(BK_MOMENTS, MSGPM_T_FEATURES);
+    if (P.iters > 0) add(BK_MOMENTS, MSGPM_T_PM_LIST);
     for (int it = 0; it < P.iters; ++it)
       for (int colour = 0; colour < 2; ++colour) {
         const int mode = search_mode(P, l + 1, it);
