@@ -38,21 +38,59 @@ namespace msgpm {
 // A workgroup owns up to kCostSlots pixels: a tile of the frame (whose patches
 // overlap), or a run of a list.  One lane per pixel takes its target and its
 // plane's local motion (FP64) into LDS; then the lane groups take the selected
-// pixels in turn, so that none sits idle for a pixel without a plane.  One
-// group per pixel of a row of the frame instead, each of its lanes computing the
-// motion: the final refresh of a 1280x544 pair with the outputs took 590 us, now
-// 428 (FP16 546, now 290); where few pixels are assigned, 512x384, 47 us, now 53
-// (FP16 36, now 37).
+// pixels in turn, in rounds of 28 at r = 4, so that none sits idle for a pixel
+// without a plane.
+//
+// Bound: dense frames by the gathers; few selected pixels by the latency of a
+// workgroup, which waits for memory with every three rows of every round.  The
+// selected pixels lie in clusters of whole windows, so that few workgroups have
+// them all.  Refresh of the assigned pixels of a pair (mode 2, r = 4, FP32; 3 % and
+// all assigned), in brackets with one lane group per pixel of a row and the motion
+// computed by each of its lanes:
+//    128x96  10 and 17 us (12, 19)     512x384  33 and 148 us (23, 163)
+//   320x240  18 and 64 us (17, 70)    1024x436  46 and 331 us (51, 359)
+//                                     2048x872 101 and 1277 us (187, 1413)
 // ---------------------------------------------------------------------------
-constexpr int kCostSlots = 128, kCostTileW = 16;
+constexpr int kCostSlots = 168;
 
-// Pixels of a workgroup: fewer where a frame would leave compute units without
-// one.  Unassigned pixels (FP32, mode 1, with the lists) with 128, 64 and 32 pixels:
-// 128x96 38, 33 and 26 us, 320x240 68, 53 and 57 us, 512x384 115, 102 and 111 us;
-// assigned ones of a 512x384 pair (mode 2, with the outputs) 57, 63 and 81 us.
-__host__ __device__ inline int cost_slots(const DevParams& P) {
-  const int n = P.W * P.H;
-  return n >= 98304 ? kCostSlots : (n >= 32768 ? 64 : 32);
+// Lane groups of a workgroup: the pixels of one round.
+__host__ __device__ constexpr int cost_round(int r) { return kWave / (2 * r + 1) * (kBlock / kWave); }
+__host__ __device__ constexpr int whole_rounds(int r, int pixels) {
+  return (pixels + cost_round(r) - 1) / cost_round(r) * cost_round(r);
+}
+static_assert(whole_rounds(1, 128) <= kCostSlots && whole_rounds(2, 128) <= kCostSlots &&
+                  whole_rounds(3, 128) <= kCostSlots && whole_rounds(4, 128) <= kCostSlots,
+              "pixels of a workgroup");
+
+// Tile of a workgroup.  Small frames: whole rounds, one or two, as a round of few
+// pixels takes as long as a full one: of 64 pixels the third round is nearly empty
+// (320x240 with 3 % assigned 22 us, with 56 pixels 18 us; 128x96 with 32 pixels 15
+// us, with 28 10 us).  Larger frames: 128 pixels, which cost least where nothing
+// is selected.  skew: by how many columns each row of tiles is turned on from the
+// one above, so that the tiles of a column, which hold a cluster, are 9
+// workgroups of an XCD apart (modulo its 32 compute units).  Without it the 32 or
+// 64 tiles of a row of a 512 or 1024 pixels wide frame put a whole column on one
+// compute unit: 42 instead of 33 us for 3 % of 512x384, 52 instead of 46 us of
+// 1024x436.  Small frames lose by it (320x240 18 -> 20 us).
+struct CostTile {
+  int cols, rows, skew;
+};
+__host__ __device__ inline CostTile cost_tile(int r, int W, int H) {
+  const int n = W * H;
+  if (n >= 98304) return CostTile{16, 8, (((W + 15) >> 4) - 9) & 31};
+  const int cols = r == 4 ? 14 : 12;  // which divide a round
+  return CostTile{cols, whole_rounds(r, n < 32768 ? 28 : 56) / cols, 0};
+}
+
+// Pixels of a run of a list of cnt: one round until there are kCostRuns runs (of
+// each of the four lists), then more rounds, up to what covers 128 pixels.  Runs of
+// 32 to 128 pixels by the frame alone took 48 instead of 37 us for the 3 % unassigned
+// pixels of a 1024x436 pair, 32 instead of 22 us at 512x384; all of them 361
+// instead of 347 us.
+constexpr int kCostRuns = 512;
+__host__ __device__ inline int cost_run(int r, unsigned cnt) {
+  const unsigned even = (cnt + kCostRuns - 1) / kCostRuns;
+  return whole_rounds(r, even > 128u ? 128 : (even > 1u ? (int)even : 1));
 }
 
 struct CostLds {
@@ -72,8 +110,7 @@ __device__ __forceinline__ void eval_cost_body(const DevParams& P, const Ws& w, 
   const int dir = bk.y;
   const int W = P.W, H = P.H;
   // this lane's pixel
-  const int slots = cost_slots(P);
-  bool act = t < slots;
+  bool act = true;
   int x = 0, y = 0;
   if (mode == 1) {
     // the unassigned pixels, from the restricted pass's lists (both colours):
@@ -81,20 +118,23 @@ __device__ __forceinline__ void eval_cost_body(const DevParams& P, const Ws& w, 
     // over the front lists; each colour takes its own run of workgroups
     const unsigned c0 = w.act_count[2 * (2 * dir) + (IDENT ? 1 : 0)];
     const unsigned c1 = w.act_count[2 * (2 * dir + 1) + (IDENT ? 1 : 0)];
-    const int nb0 = (int)((c0 + slots - 1) / slots), nb1 = (int)((c1 + slots - 1) / slots);
+    const int run0 = cost_run(R, c0), run1 = cost_run(R, c1);
+    const int nb0 = (int)((c0 + run0 - 1) / run0), nb1 = (int)((c1 + run1 - 1) / run1);
     if (bk.x >= nb0 + nb1) return;
-    const int colour = bk.x < nb0 ? 0 : 1;
-    const unsigned i = (unsigned)xcd_remap(colour ? bk.x - nb0 : bk.x, colour ? nb1 : nb0) * slots + t;
-    act = act && i < (colour ? c1 : c0);
+    const int colour = bk.x < nb0 ? 0 : 1, run = colour ? run1 : run0;
+    const unsigned i = (unsigned)xcd_remap(colour ? bk.x - nb0 : bk.x, colour ? nb1 : nb0) * run + t;
+    act = t < run && i < (colour ? c1 : c0);
     const unsigned cap = (unsigned)((W + 1) >> 1) * (unsigned)H;
     const int q = act ? w.act[2 * dir + colour][IDENT ? cap - 1u - i : i] : 0;
     y = q / W;
     x = q - y * W;
   } else {
-    const int ntx = (W + kCostTileW - 1) / kCostTileW, b = xcd_remap(bk.x, bk.nx);
-    x = b % ntx * kCostTileW + t % kCostTileW;
-    y = b / ntx * (slots / kCostTileW) + t / kCostTileW;
-    act = act && x < W && y < H;
+    const CostTile T = cost_tile(R, W, H);
+    const int ntx = (W + T.cols - 1) / T.cols, b = xcd_remap(bk.x, bk.nx);
+    const int row = b / ntx, col = (b - row * ntx + T.skew * row) % ntx;
+    x = col * T.cols + t % T.cols;
+    y = row * T.rows + t / T.cols;
+    act = t < T.cols * T.rows && x < W && y < H;
   }
   const int p = y * W + x;
   int label = -1;
@@ -105,7 +145,7 @@ __device__ __forceinline__ void eval_cost_body(const DevParams& P, const Ws& w, 
   if (t == 0) S.n = 0;
   __syncthreads();
   int slot = 0;
-  if (wave < kCostSlots / kWave) {
+  if (wave < (kCostSlots + kWave - 1) / kWave) {
     const unsigned long long m = __ballot(act);
     int first = 0;
     if (lane == 0) first = atomicAdd(&S.n, __popcll(m));
@@ -125,6 +165,10 @@ __device__ __forceinline__ void eval_cost_body(const DevParams& P, const Ws& w, 
   }
   __syncthreads();
   const int n = S.n;
+  if (n == 0) {
+    __syncthreads();  // a persistent launch clears S.n for its next workgroup
+    return;
+  }
   const Feat F1 = feat_buf<C, FP16>(w.feat[dir], W, H), F2 = feat_buf<C, FP16>(w.feat[1 - dir], W, H);
   for (int i0 = wave * NG; i0 < n; i0 += NG * (kBlock / kWave)) {
     const int i = i0 + g;
@@ -157,7 +201,8 @@ __device__ __forceinline__ void eval_cost_body(const DevParams& P, const Ws& w, 
   }
   __syncthreads();
   if (act) w.cost[dir][p] = S.cost[slot];
-  count_evals<true>(w.counters, 2 + dir, act ? 1u : 0u);
+  if (t == 0)
+    atomicAdd(&w.counters[(2 + dir) * kCounterStripes + (blockIdx.x & (kCounterStripes - 1))], (unsigned long long)n);
 }
 
 // Waves per SIMD the registers of distorted patches are held to: a final refresh
@@ -711,9 +756,15 @@ hipError_t launch_pm_lists(const DevParams& P, const Ws& w, bool cleared, hipStr
 // Workgroups of one direction of a cost refresh: tiles, or (mode 1) runs of both
 // colours' lists.
 static int cost_blocks(const DevParams& P, int mode) {
-  const int slots = cost_slots(P), th = slots / kCostTileW;
-  if (mode == 1) return 2 * ((((P.W + 1) >> 1) * P.H + slots - 1) / slots);
-  return ((P.W + kCostTileW - 1) / kCostTileW) * ((P.H + th - 1) / th);
+  if (mode == 1) {
+    // a list has at most kCostRuns runs or, where those are of the most pixels, what covers it
+    const int half = ((P.W + 1) >> 1) * P.H, one = whole_rounds(P.r, 1), most = whole_rounds(P.r, 128);
+    const int short_runs = (half + one - 1) / one, long_runs = (half + most - 1) / most;
+    const int few = short_runs < kCostRuns ? short_runs : kCostRuns;
+    return 2 * (few > long_runs ? few : long_runs);
+  }
+  const CostTile T = cost_tile(P.r, P.W, P.H);
+  return ((P.W + T.cols - 1) / T.cols) * ((P.H + T.rows - 1) / T.rows);
 }
 
 template <int R, int C, bool FP16, bool IDENT>
