@@ -447,7 +447,7 @@ def main() -> int:
                     help="time eager launches only (default: the pipeline as one captured HIP graph per step, "
                          "plus an eager pass with HIP events around every launch for the per-kernel figures)")
     ap.add_argument("--fp16", action="store_true", help="FP16 feature storage (FP32 accumulation)")
-    ap.add_argument("--two-streams", action="store_true",
+    ap.add_argument("--one-launch", "--two-streams", dest="one_launch", action="store_true",
                     help="restricted half-sweeps as the library runs them by default, as one launch, "
                          "instead of as two in sequence")
     ap.add_argument("--seed", type=int, default=0, help="scene seed of the 1024x436 generator")
@@ -488,7 +488,7 @@ def main() -> int:
     f1 = torch.from_numpy(pair.frame1).cuda()
     f2 = torch.from_numpy(pair.frame2).cuda()
     params = dict(PARAMS, fp16=args.fp16, cue_overlap=args.cues, cue_unique=args.cues, fill_sweeps=args.fill,
-                  histeq=args.histeq, merge_strict=args.strict, one_stream=not args.two_streams)
+                  histeq=args.histeq, merge_strict=args.strict, one_stream=not args.one_launch)
     g = msgpm.Pair(W, H, **params)
     flows = [torch.empty((H, W, 2), dtype=torch.float32, device="cuda") for _ in range(2)]
     occs = [torch.empty((H, W), dtype=torch.uint8, device="cuda") for _ in range(2)]
@@ -557,10 +557,10 @@ def main() -> int:
 
     # each PatchMatch kernel on its own: by default the restricted half-sweeps
     # run as two launches in sequence (MSGPM_FLAG_ONE_STREAM), so the timed
-    # eager steps give each kernel's own time; with --two-streams they are one
+    # eager steps give each kernel's own time; with --one-launch they are one
     # launch there, and an equal number of two-launch steps is timed
     alone_ms, alone_n = kernel_ms, launches
-    if args.two_streams:
+    if args.one_launch:
         g1 = msgpm.Pair(W, H, **dict(params, one_stream=True))
         g1.solve(f1, f2)
         torch.cuda.synchronize()
@@ -657,7 +657,7 @@ def main() -> int:
                    "width": W, "height": H, "seed": args.seed, "fp16_storage": bool(args.fp16),
                    "occlusion_cues_2_3": bool(args.cues), "fill_sweeps": args.fill, "histeq": bool(args.histeq),
                    "merge_strict": bool(args.strict), "independent_quads": bool(args.independent),
-                   "restricted_launches": "two streams" if args.two_streams else "one stream"},
+                   "restricted_launches": "one for both lists" if args.one_launch else "two in sequence"},
         "patch_evals_per_s": round((ev["pm_init"] + ev["pm_restricted"] + ev["pm_restricted_ident"])
                                    / (ms_per_step * 1e-3), 1),
         # the initial pass alone: its evaluations over its kernel time, beside the

@@ -205,8 +205,9 @@ msgpm_status msgpm_solve(const msgpm_params* p, const float* d_rgb1, const float
 
 /* ---------------------------------------------------------------------------
  * Phase entry points.  Each runs one step of the pipeline on the state held in
- * the workspace, for both directions, exactly as msgpm_solve does; together
- * they let a caller run, inspect or replace the state between steps.
+ * the workspace, for both directions, with the result that the step has in
+ * msgpm_solve, bit for bit; together they let a caller run, inspect or replace the
+ * state between steps.
  * ------------------------------------------------------------------------- */
 
 /* Features of both frames (pixel colours plus optional luma gradients gx, gy
@@ -241,8 +242,8 @@ msgpm_status msgpm_eval_cost(const msgpm_params* p, void* d_ws, int mode, void* 
    current cost is then computed first, exactly as msgpm_eval_cost (mode 0
    for restricted = 0, mode 1 for restricted = 1) would compute it, instead of
    being read from the workspace; the result equals that refresh followed by
-   the plain half-sweep, over this colour's pixels.  msgpm_solve uses it for
-   the first half-sweep of each colour in every pass.  Any other value of
+   the plain half-sweep, over this colour's pixels.  The first half-sweep of
+   each colour in every pass of msgpm_solve works so.  Any other value of
    restricted is MSGPM_E_INVALID. */
 #define MSGPM_PM_FRESH 2
 msgpm_status msgpm_pm_halfsweep(const msgpm_params* p, void* d_ws, int colour, int iter, int slot, int restricted,

@@ -31,7 +31,7 @@ __device__ inline Feat feat_buf(const void* F, int W, int H) {
 }
 
 // Feature access.  FP32: C floats per pixel; FP16: C=3 -> 4 halves, C=5 -> 6
-// halves per pixel.  load1 reads pixel idx, load2 pixels idx and idx + 1 with
+// halves per pixel.  load1 reads pixel idx; raw2 pixels idx and idx + 1 with
 // one contiguous access (the buffer is padded so idx + 1 always exists).
 template <int C, bool FP16>
 struct Px {
@@ -92,34 +92,6 @@ struct Px {
     } else {
       const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(F.r, o, 0, 0);
       u[0] = a.x; u[1] = a.y; u[2] = a.z; u[3] = a.w;
-    }
-  }
-  static __device__ inline void load2(Feat F, int idx, float* v, float* w) {
-    const int o = idx * kBytes;
-    if constexpr (!FP16) {
-      if constexpr (C == 3) {
-        const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(F.r, o, 0, 0);
-        const u32x2 b = __builtin_amdgcn_raw_buffer_load_b64(F.r, o + 16, 0, 0);
-        v[0] = uf(a.x); v[1] = uf(a.y); v[2] = uf(a.z); w[0] = uf(a.w); w[1] = uf(b.x); w[2] = uf(b.y);
-      } else {
-        const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(F.r, o, 0, 0);
-        const u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(F.r, o + 16, 0, 0);
-        const u32x2 c = __builtin_amdgcn_raw_buffer_load_b64(F.r, o + 32, 0, 0);
-        v[0] = uf(a.x); v[1] = uf(a.y); v[2] = uf(a.z); v[3] = uf(a.w); v[4] = uf(b.x);
-        w[0] = uf(b.y); w[1] = uf(b.z); w[2] = uf(b.w); w[3] = uf(c.x); w[4] = uf(c.y);
-      }
-    } else {
-      if constexpr (C == 3) {
-        const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(F.r, o, 0, 0);
-        const float2 a = h2f(u.x), b = h2f(u.y), c = h2f(u.z), d = h2f(u.w);
-        v[0] = a.x; v[1] = a.y; v[2] = b.x; w[0] = c.x; w[1] = c.y; w[2] = d.x;
-      } else {
-        const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(F.r, o, 0, 0);
-        const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(F.r, o + 16, 0, 0);
-        const float2 a = h2f(u.x), b = h2f(u.y), c = h2f(u.z), d = h2f(u.w), e = h2f(t.x), f = h2f(t.y);
-        v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y; v[4] = c.x;
-        w[0] = d.x; w[1] = d.y; w[2] = e.x; w[3] = e.y; w[4] = f.x;
-      }
     }
   }
 };

@@ -1,4 +1,7 @@
-// Warped-patch SSD and PatchMatch half-sweeps (the per-pixel hot loop).
+// Warped-patch costs: the cost refresh, the pixel lists of the restricted
+// half-sweeps, and the half-sweep of a single call (msgpm_pm_halfsweep), which
+// evaluates every candidate.  The passes of a whole solve, which evaluate only
+// those that could win, are in search.h.
 //
 // Cost C(p, t, H): sum over the (2r+1)^2 taps d of the square patch of p of
 //   sum_c w_c (F1_c(clamp(p + d)) - bilinear F2_c(t + Delta(d)))^2,
@@ -15,9 +18,9 @@
 // contiguous load (features are stored interleaved per pixel); integral
 // geometries (identity, integer translations) fetch one pixel per tap.  Column
 // partials are combined across the group in a fixed order, so every lane of the
-// group takes the same decisions.  Identity-patch candidates are evaluated in
-// batches whose first rows are gathered together, each then finished on its
-// own; distorted-patch candidates one at a time; both with exact early
+// group takes the same decisions.  The single half-sweep evaluates identity-patch
+// candidates in batches whose first rows are gathered together, each then finished
+// on its own, and distorted-patch candidates one at a time; both with exact early
 // rejections on partial sums (every schedule takes the decisions of a
 // one-at-a-time loop).  Costs are accumulated in FP32; FP16 records are
 // widened inside mixed-precision multiply-adds.
