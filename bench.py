@@ -61,12 +61,12 @@ PEAK_LDS_GBS = 78643.2
 # kernels as they are now.
 TRAFFIC = {
     # profiles/k_search_1024x436_traffic.md
-    ("k_search (identity patches, initial pass)", False): 1.3864e9,
-    ("k_search (identity patches, restricted)", False): 2.1476e8,
-    ("k_search (distorted patches)", False): 3.3009e8,
-    ("k_search (identity patches, initial pass)", True): 7.6789e8,
-    ("k_search (identity patches, restricted)", True): 1.4938e8,
-    ("k_search (distorted patches)", True): 1.9570e8,
+    ("k_search (identity patches, initial pass)", False): 1.4098e9,
+    ("k_search (identity patches, restricted)", False): 2.1958e8,
+    ("k_search (distorted patches)", False): 3.3095e8,
+    ("k_search (identity patches, initial pass)", True): 7.9250e8,
+    ("k_search (identity patches, restricted)", True): 1.5405e8,
+    ("k_search (distorted patches)", True): 1.9540e8,
 }
 
 
